@@ -12,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 OUT = os.path.join(HERE, "libqops.so")
 OBJ = os.path.join(HERE, "_build")
 
-SOURCES = ["kernels.hip", "mlp.hip", "planner.cpp", "runtime.cpp", "costmodel.cpp", "profile.cpp", "batch.cpp", "readout.hip", "fold.cpp",
+SOURCES = ["kernels.hip", "regtile.hip", "mlp.hip", "planner.cpp", "runtime.cpp", "costmodel.cpp", "profile.cpp", "batch.cpp", "readout.hip", "fold.cpp",
            "noalloc.hip", "tier.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -41,7 +41,7 @@ def _compile(src: str) -> str:
     return obj
 
 
-def build(jobs: int = 4) -> str:
+def build(jobs: int = 8) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         objs = list(ex.map(_compile, SOURCES))
