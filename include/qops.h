@@ -449,7 +449,7 @@ int32_t qops_batch_results(qops_batch_exec* e, double* out_expz);
 /* Mean device time of `reps` back-to-back graph launches (blocking). */
 int32_t qops_batch_time(qops_batch_exec* e, int32_t reps, double* seconds);
 /* New angles / matrices for every circuit (same structure): re-composes the
- * fused operations in FP64 and replaces the coefficients the graph reads;
+ * fused operations in FP64 and replaces the program the graph reads;
  * QOPS_BAD_STATE if the structure changed. */
 int32_t qops_batch_update(qops_batch_exec* e, const qops_gate* const* gates, const size_t* n_gates);
 /* Shape the executor chose; frees an executor (null accepted). */

@@ -14,6 +14,12 @@ OBJ = os.path.join(HERE, "_build")
 
 SOURCES = ["kernels.hip", "regtile.hip", "mlp.hip", "planner.cpp", "runtime.cpp", "costmodel.cpp", "profile.cpp", "batch.cpp", "readout.hip", "fold.cpp",
            "noalloc.hip", "tier.cpp"]
+# register tile variants (precision, register bits, wave bits): one object
+# each, as in QOPS_TILE_VARIANTS of regtile.hpp
+# The operation loop branches on wave-uniform values only; structurizing those
+# branches would pass the whole tile through merge blocks that copy it.
+REG_TILE_FLAGS = ["-mllvm", "-structurizecfg-skip-uniform-regions=true"]
+REG_TILES = [(t, r, w) for r in (5, 4) for t in ("double", "float") for w in (2, 1, 0)]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -28,10 +34,11 @@ FLAGS = [
 ]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(OBJ, src + ".o")
+def _compile(unit) -> str:
+    src, defines, name = unit
+    obj = os.path.join(OBJ, name + ".o")
     path = os.path.join(CSRC, src)
-    cmd = [HIPCC] + FLAGS + ["-c", path, "-o", obj]
+    cmd = [HIPCC] + FLAGS + defines + ["-c", path, "-o", obj]
     if src.endswith(".cpp"):
         cmd = [HIPCC] + [f for f in FLAGS if f != "--offload-arch=gfx950"] + ["-x", "hip", "--offload-arch=gfx950", "-c", path, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -41,10 +48,17 @@ def _compile(src: str) -> str:
     return obj
 
 
+def units():
+    """(source, defines, object name) of every object, the slowest first."""
+    u = [("regtile.hip", REG_TILE_FLAGS + [f"-DQOPS_RT_T={t}", f"-DQOPS_RT_R={r}", f"-DQOPS_RT_W={w}"],
+          f"regtile_{t}_{r}_{w}.hip") for t, r, w in REG_TILES]
+    return [(SOURCES[0], [], SOURCES[0])] + u + [(s, [], s) for s in SOURCES[1:]]
+
+
 def build(jobs: int = 8) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+        objs = list(ex.map(_compile, units()))
     tmp = OUT + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -98,12 +98,38 @@ void cast_coef(const std::vector<double>& src, std::vector<unsigned char>& dst, 
     for (size_t i = 0; i < src.size(); ++i) d[i] = (T)src[i];
 }
 
+// Headers and operations of every circuit, their offsets moved to the batch's
+// images (coefficients first at coef_base[i]).
+void program_images(const qops_batch_exec* e, std::vector<PassHdr>& hdrs, std::vector<DevOp>& ops)
+{
+    hdrs.clear();
+    ops.clear();
+    for (int i = 0; i < e->count; ++i) {
+        const Plan& p = e->plans[i];
+        const int op_base = (int)ops.size();
+        const int32_t coef_n = (int32_t)e->coef_base[i];
+        for (DevOp d : p.dops) {
+            // LDS-tile ops with b = 1 address the pass's staged coefficients
+            const bool staged = d.b && (d.type == OP_MFMA || d.type == OP_DIAG_LDS || d.type == OP_DENSE_LDS);
+            d.coef += staged ? 0 : coef_n;
+            ops.push_back(d);
+        }
+        if (p.n <= e->small_max_n) continue;
+        for (const PassPlan& pp : p.passes) {
+            PassHdr h = p.hdrs[pp.hdr];
+            h.op0 += op_base;
+            h.coef_src += coef_n;
+            hdrs.push_back(h);
+        }
+    }
+}
+
 int32_t layout(qops_batch_exec* e)
 {
     const size_t asz = e->prec == QOPS_C64 ? 8 : 16, csz = asz / 2;
     std::vector<PassHdr> hdrs;
     std::vector<DevOp> ops;
-    size_t coef_n = 0;
+    size_t coef_n = 0, op_n = 0, hdr_n = 0;
     e->coef_base.assign(e->count, 0);
     e->state_base.assign(e->count, 0);
     e->circs.assign(e->count, BatchCirc{});
@@ -118,28 +144,16 @@ int32_t layout(qops_batch_exec* e)
         c.out0 = (int32_t)out0;
         out0 += p.n;
         e->coef_base[i] = coef_n;
-        const int op_base = (int)ops.size();
-        for (DevOp d : p.dops) {
-            // LDS-tile ops with b = 1 address the pass's staged coefficients
-            const bool staged = d.b && (d.type == OP_MFMA || d.type == OP_DIAG_LDS || d.type == OP_DENSE_LDS);
-            d.coef += staged ? 0 : (int32_t)coef_n;
-            ops.push_back(d);
-        }
         if (p.n <= e->small_max_n) {
-            c.op0 = op_base + (p.passes.empty() ? 0 : p.passes[0].op0);
+            c.op0 = (int32_t)op_n + (p.passes.empty() ? 0 : p.passes[0].op0);
             c.nops = p.passes.empty() ? 0 : p.passes[0].nops;
             c.npass = 0;
             e->small_ids.push_back(i);
             max_small_n = std::max(max_small_n, p.n);
         } else {
-            c.hdr0 = (int32_t)hdrs.size();
+            c.hdr0 = (int32_t)hdr_n;
             c.npass = (int32_t)p.passes.size();
-            for (const PassPlan& pp : p.passes) {
-                PassHdr h = p.hdrs[pp.hdr];
-                h.op0 += op_base;
-                h.coef_src += (int32_t)coef_n;
-                hdrs.push_back(h);
-            }
+            hdr_n += p.passes.size();
             maxpass = std::max(maxpass, c.npass);
             c.part0 = (int32_t)part0;
             const int s = std::min(p.n, 13);
@@ -149,7 +163,9 @@ int32_t layout(qops_batch_exec* e)
             e->big_ids.push_back(i);
         }
         coef_n += p.coef.size();
+        op_n += p.dops.size();
     }
+    program_images(e, hdrs, ops);
     e->total_out = out0;
     e->total_part = part0;
     e->total_state_bytes = state_off;
@@ -386,16 +402,24 @@ int32_t qops_batch_update(qops_batch_exec* e, const qops_gate* const* gates, con
         cimg.assign(std::max<size_t>(total, 1) * csz, 0);
         for (int i = 0; i < e->count; ++i) {
             qops::Plan& p = e->plans[i];
-            const size_t before_ops = p.dops.size(), before_coef = p.coef.size();
+            const size_t before_ops = p.dops.size(), before_coef = p.coef.size(), before_hdrs = p.hdrs.size();
             Err er = update_plan(p, gates[i], n_gates[i]);
             if (!er.ok()) return set_error(er.code, "circuit " + std::to_string(i) + ": " + er.msg);
-            if (p.dops.size() != before_ops || p.coef.size() != before_coef)
+            if (p.dops.size() != before_ops || p.coef.size() != before_coef || p.hdrs.size() != before_hdrs)
                 return set_error(QOPS_BAD_STATE, "circuit " + std::to_string(i) + ": new parameters change the plan");
             if (e->prec == QOPS_C64) cast_coef<float>(p.coef, cimg, e->coef_base[i]);
             else cast_coef<double>(p.coef, cimg, e->coef_base[i]);
         }
+        // the sheared operations' forms and the pass factors follow the values
+        std::vector<PassHdr> hdrs;
+        std::vector<DevOp> ops;
+        program_images(e, hdrs, ops);
         hipError_t er = hipStreamSynchronize(e->stream);
         if (er == hipSuccess) er = hipMemcpy(e->d_coef, cimg.data(), total * csz, hipMemcpyHostToDevice);
+        if (er == hipSuccess && !ops.empty())
+            er = hipMemcpy(e->d_ops, ops.data(), ops.size() * sizeof(DevOp), hipMemcpyHostToDevice);
+        if (er == hipSuccess && !hdrs.empty())
+            er = hipMemcpy(e->d_hdrs, hdrs.data(), hdrs.size() * sizeof(PassHdr), hipMemcpyHostToDevice);
         if (er != hipSuccess) return hip_fail(er, "batch update");
         return QOPS_OK;
     } catch (...) {

@@ -13,13 +13,22 @@ enum OpType : int32_t {
     OP_1Q_LANE = 2,   // 2x2 on a lane bit (shuffles)    a = lane bit (0..5)
     OP_DIAG = 3,      // diagonal table over m bits      a = m, pos[i] = encoded source of bit i
     OP_REMAP = 4,     // registers -> LDS -> registers   b = new mapping
-    OP_TO_LDS = 5,    // registers -> LDS
-    OP_FROM_LDS = 6,  // LDS -> registers                b = new mapping
     OP_DENSE_LDS = 7, // 2^k x 2^k on tile positions, vector ALU, in LDS   a = k, pos = tile positions
     OP_MFMA = 8,      // 2^k x 2^k on tile positions, matrix cores, in LDS  a = k, pos = tile positions
     OP_DIAG_LDS = 9,  // diagonal table on tile positions, in LDS (whole-state kernel)
-    OP_CPHASE = 10    // phase coef on amplitudes whose masked bits are all 1   b = 1: phase is -1
+    OP_CPHASE = 10,   // phase coef on amplitudes whose masked bits are all 1   b = 1: phase is -1
+    OP_SHEAR_REG = 11,   // sheared 2x2 on a register bit  a = register bit, b = form, c_lane = coefficient type
+    OP_SHEAR_LANE = 12   // scaled 2x2 on a lane bit       a = lane bit, b = 1: exchanged, c_lane = coefficient type
 };
+// Register tile passes.  A 2x2 whose bit is next targeted by another
+// uncontrolled 2x2 runs in a two-coefficient form (coef: w, v; type 0 =
+// complex, 1 = real, 2 = imaginary) that leaves a diagonal factor on the bit,
+// and for register bits possibly exchanged slots; the planner folds the
+// factor into that next 2x2.  Register bits with exchanged slots ("flipped":
+// slot bit = 1 - bit) are resolved in the operations that read the slot
+// index: c_reg controls hold where slot & c_reg == c_tile (OP_1Q_*,
+// OP_CPHASE), OP_DIAG starts its table index at c_tile, OP_REMAP
+// carries the flipped register bits in c_reg, the store in PassHdr::flip.
 // OP_1Q_REG / OP_1Q_LANE: b = 1 marks an exact X (pure exchange, no arithmetic).
 // OP_MFMA / OP_DIAG_LDS / OP_DENSE_LDS in an LDS tile pass: b = 1 means `coef` is an offset
 // into the coefficients staged in LDS, b = 0 an offset into global memory.
@@ -80,6 +89,8 @@ struct PassHdr {
     int32_t run_gshift[QOPS_MAX_RUNS]; // bit offset of the run inside the tile number
     int32_t hoist;                  // LDS tile pass: op (relative to op0) whose matrix-core
                                     //   fragments stay in registers, or -1
+    int32_t flip;                   // register tile pass: register bits stored with exchanged slots
+    double scale;                   // register tile pass: factor on every stored amplitude
 };
 
 // Batched executor records.

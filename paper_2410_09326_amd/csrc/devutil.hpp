@@ -70,6 +70,10 @@ __device__ __forceinline__ typename CxT<T>::V ldc(const T* __restrict__ c, int i
     return v;
 }
 
+// Fused multiply-add in the state precision.
+__device__ __forceinline__ float fmat(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fmat(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // LDS slot of tile element e: the low five bits (32 amplitudes = one row of
 // the 64 four-byte banks for complex64) are XORed with the next five, so
 // that strided groups and matrix-core column sets spread over the banks.

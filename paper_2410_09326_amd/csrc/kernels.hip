@@ -25,10 +25,6 @@ namespace qops {
 // LDS-resident operations (tile of 2^L amplitudes at `lds`)
 // ---------------------------------------------------------------------------
 
-// Fused multiply-add in the state precision.
-__device__ __forceinline__ float fmat(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fmat(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
 // Dense 2^K x 2^K on tile positions pos[0..K-1] (matrix bit order), vector
 // ALU.  Every thread handles whole groups.  Group g of the tile has its
 // target bits zero and its other bits taken from g in order; the insertion

@@ -914,8 +914,118 @@ static void emit_lds_op(Plan& p, const LOp& o, int L, F tpos, PassPlan& pp, bool
     p.dops.push_back(d);
 }
 
+// Sheared 2x2 operations of the register tile kernel.  A 2x2 M on a bit that
+// an uncontrolled 2x2 targets again (no other non-diagonal operation on the
+// bit in between) is replaced by a product of two triangular steps that cost
+// half of M's multiply-adds; M = (exchange) diag(d0, d1) (steps).  The
+// diagonal commutes with every operation up to that next 2x2 (controls,
+// phases, other bits), which absorbs it into its own matrix, and the last 2x2
+// of each such chain is applied in full.  `pend` holds the diagonal waiting on
+// each physical bit, with |d0 d1| = 1 at pass ends (the common factor moves to
+// the pass's store).  Everything is composed in FP64.
+struct Chain {
+    std::vector<char> shear;    // per lowered operation: a later 2x2 absorbs its diagonal
+    cd d0[64], d1[64];
+    double scale = 1.0;         // factor the current pass still owes
+    Chain()
+    {
+        for (int b = 0; b < 64; ++b) d0[b] = d1[b] = cd(1);
+    }
+};
+
+static bool unitary2(const std::vector<cd>& m)
+{
+    const double n0 = std::norm(m[0]) + std::norm(m[2]), n1 = std::norm(m[1]) + std::norm(m[3]);
+    return std::abs(n0 - 1.0) < 1e-9 && std::abs(n1 - 1.0) < 1e-9 &&
+           std::abs(std::conj(m[0]) * m[1] + std::conj(m[2]) * m[3]) < 1e-9;
+}
+
+// Operations whose diagonal a later one absorbs, in execution order.
+static void find_chains(const Plan& p, Chain& ch)
+{
+    ch.shear.assign(p.lops.size(), 0);
+    bool absorbs[64] = {false};
+    for (size_t pi = p.passes.size(); pi-- > 0;) {
+        const PassPlan& pp = p.passes[pi];
+        for (size_t i = pp.lop.size(); i-- > 0;) {
+            const LOp& o = p.lops[pp.lop[i]];
+            if (o.kind == LOp::DIAG) continue;
+            if (pp.type == PASS_TILE_REG && o.kind == LOp::ONEQ && o.cmask == 0) {
+                ch.shear[pp.lop[i]] = absorbs[o.t[0]] && unitary2(o.m);
+                absorbs[o.t[0]] = true;
+            } else {
+                for (int j = 0; j < o.k; ++j) absorbs[o.t[j]] = false;
+            }
+        }
+    }
+}
+
+static int coef_type(cd w, cd v)
+{
+    if (w.imag() == 0.0 && v.imag() == 0.0) return 1;
+    if (w.real() == 0.0 && v.real() == 0.0) return 2;
+    return 0;
+}
+
+// Form of a sheared 2x2 on a register bit: N maps the slots (0, 1) to bit
+// values (0, 1).  The pivot is the larger entry of the row, so |w|, |v| stay
+// near or below 1; of the two orders the one that keeps |d1/d0| nearer to 1
+// is taken, so the waiting diagonals stay within a factor of 2.
+static void shear_reg_form(const cd (&N)[4], int& form, int& flip, cd& w, cd& v, cd& d0, cd& d1)
+{
+    const cd det = N[0] * N[3] - N[1] * N[2];
+    const double c0 = std::norm(N[0]) + std::norm(N[2]), c1 = std::norm(N[1]) + std::norm(N[3]);
+    if (std::norm(N[0]) * c1 >= std::norm(N[1]) * c0) {
+        flip = 0;
+        const double ra = std::abs(std::log(std::abs(det / (N[0] * N[0]))));
+        const double rb = std::abs(std::log(std::abs(det / (N[3] * N[3]))));
+        if (ra <= rb) {           // slot 0 first
+            form = 0;
+            d0 = N[0];
+            d1 = det / N[0];
+            w = N[1] / N[0];
+            v = N[2] / d1;
+        } else {                  // slot 1 first
+            form = 1;
+            d1 = N[3];
+            d0 = det / N[3];
+            w = N[2] / N[3];
+            v = N[1] / d0;
+        }
+    } else {                      // slot 0 ends as bit value 1, slot 1 as 0
+        flip = 1;
+        const double ra = std::abs(std::log(std::abs(det / (N[1] * N[1]))));
+        const double rb = std::abs(std::log(std::abs(det / (N[2] * N[2]))));
+        if (ra <= rb) {           // slot 1 first
+            form = 1;
+            d0 = N[1];
+            d1 = -det / N[1];
+            w = N[0] / N[1];
+            v = N[3] / d1;
+        } else {                  // slot 0 first
+            form = 0;
+            d1 = N[2];
+            d0 = -det / N[2];
+            w = N[3] / N[2];
+            v = N[0] / d0;
+        }
+    }
+}
+
+// Scaled form on a lane bit (no slots to exchange: the exchanged form takes
+// the partner's amplitude as its own).
+static void shear_lane_form(const cd (&N)[4], int& ex, cd& w, cd& v, cd& d0, cd& d1)
+{
+    const double c0 = std::norm(N[0]) + std::norm(N[2]), c1 = std::norm(N[1]) + std::norm(N[3]);
+    ex = std::norm(N[0]) * c1 >= std::norm(N[1]) * c0 ? 0 : 1;
+    d0 = ex ? N[1] : N[0];
+    d1 = ex ? N[2] : N[3];
+    w = (ex ? N[0] : N[1]) / d0;
+    v = (ex ? N[3] : N[2]) / d1;
+}
+
 // Register-tile pass: assigns register/wave bits per stage and encodes ops.
-static void emit_tile_reg(Plan& p, PassPlan& pp)
+static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
 {
     const int R = pp.R, W = pp.W, U = R + W;
     const std::vector<int>& up = pp.up;
@@ -971,6 +1081,7 @@ static void emit_tile_reg(Plan& p, PassPlan& pp)
             if (map_get(map, R + w) == u) return w;
         return -1;
     };
+    uint32_t flip = 0;            // register bits with exchanged slots
     for (size_t i = 0; i < pp.lop.size(); ++i) {
         const LOp& o = p.lops[pp.lop[i]];
         if (need[i] >= 0 && regbit(need[i]) < 0) {
@@ -980,6 +1091,8 @@ static void emit_tile_reg(Plan& p, PassPlan& pp)
             std::memset(&r, 0, sizeof(r));
             r.type = OP_REMAP;
             r.b = (int32_t)map;
+            r.c_reg = flip;       // resolved by the exchange through LDS
+            flip = 0;
             p.dops.push_back(r);
             pp.n_remaps++;
         }
@@ -1001,8 +1114,45 @@ static void emit_tile_reg(Plan& p, PassPlan& pp)
                     d.c_wave |= 1u << wavebit(u);
                 }
             }
+            d.c_tile = d.c_reg & ~flip;   // the slot value that stands for all ones
         };
-        if (o.kind == LOp::ONEQ) {
+        if (o.kind == LOp::ONEQ && o.cmask == 0) {
+            // the diagonal waiting on the bit joins the matrix
+            const int b = o.t[0];
+            cd N[4] = {o.m[0] * ch.d0[b], o.m[1] * ch.d1[b], o.m[2] * ch.d0[b], o.m[3] * ch.d1[b]};
+            ch.d0[b] = ch.d1[b] = cd(1);
+            const bool is_x = N[0] == cd(0) && N[1] == cd(1) && N[2] == cd(1) && N[3] == cd(0);
+            const bool lane = b < 6;
+            const int rb = lane ? -1 : regbit(upos(b));
+            if (!lane && (flip >> rb & 1u) && !is_x) {
+                std::swap(N[0], N[1]);
+                std::swap(N[2], N[3]);
+                flip &= ~(1u << rb);
+            }
+            d.a = lane ? b : rb;
+            if (lane) pp.n_lane_ops++;
+            else pp.n_reg_ops++;
+            if (!is_x) pp.flops += 16.0 * std::ldexp(1.0, p.n);
+            if (ch.shear[pp.lop[i]] && !is_x) {
+                cd w, v;
+                int form, fl = 0;
+                if (lane) {
+                    d.type = OP_SHEAR_LANE;
+                    shear_lane_form(N, form, w, v, ch.d0[b], ch.d1[b]);
+                } else {
+                    d.type = OP_SHEAR_REG;
+                    shear_reg_form(N, form, fl, w, v, ch.d0[b], ch.d1[b]);
+                    flip |= (uint32_t)fl << rb;
+                }
+                d.b = form;
+                d.c_lane = (uint32_t)coef_type(w, v);
+                d.coef = push_coef(p, {w, v, cd(0), cd(0)});   // as many as the full form
+            } else {
+                d.type = lane ? OP_1Q_LANE : OP_1Q_REG;
+                d.b = is_x ? 1 : 0;
+                d.coef = push_coef(p, {N[0], N[1], N[2], N[3]});
+            }
+        } else if (o.kind == LOp::ONEQ) {
             if (o.t[0] < 6) {
                 d.type = OP_1Q_LANE;
                 d.a = o.t[0];
@@ -1013,9 +1163,11 @@ static void emit_tile_reg(Plan& p, PassPlan& pp)
                 pp.n_reg_ops++;
             }
             enc_ctrl(o.cmask);
-            d.coef = push_coef(p, o.m);
             const bool is_x = o.m[0] == cd(0) && o.m[1] == cd(1) && o.m[2] == cd(1) && o.m[3] == cd(0);
             d.b = is_x ? 1 : 0;
+            std::vector<cd> m = o.m;
+            if (d.type == OP_1Q_REG && (flip >> d.a & 1u)) m = {m[3], m[2], m[1], m[0]};   // on exchanged slots
+            d.coef = push_coef(p, m);
             if (!is_x) pp.flops += 16.0 * std::ldexp(1.0, p.n - __builtin_popcountll(o.cmask));
         } else if (o.cphase) {
             // phase on the all-ones pattern of the table bits: a control mask
@@ -1039,7 +1191,10 @@ static void emit_tile_reg(Plan& p, PassPlan& pp)
                 }
                 const int u = upos(b);
                 if (u < 0) d.pos[j] = enc_src(SRC_GLOB, b);
-                else if (regbit(u) >= 0) d.pos[j] = enc_src(SRC_REG, regbit(u));
+                else if (regbit(u) >= 0) {
+                    d.pos[j] = enc_src(SRC_REG, regbit(u));
+                    if (flip >> regbit(u) & 1u) d.c_tile |= 1u << j;
+                }
                 else d.pos[j] = enc_src(SRC_WAVE, wavebit(u));
             }
             d.coef = push_coef(p, o.m);
@@ -1048,6 +1203,16 @@ static void emit_tile_reg(Plan& p, PassPlan& pp)
         }
         p.dops.push_back(d);
     }
+    // waiting diagonals keep |d0 d1| = 1; the rest is the store's factor
+    for (int b = 0; b < p.n; ++b) {
+        const double g = std::sqrt(std::abs(ch.d0[b] * ch.d1[b]));
+        ch.d0[b] /= g;
+        ch.d1[b] /= g;
+        ch.scale *= g;
+    }
+    h.flip = (int32_t)flip;
+    h.scale = ch.scale;
+    ch.scale = 1.0;
     h.nops = (int)p.dops.size() - h.op0;
     h.lds_bytes = W > 0 ? (1 << pp.L) * (p.prec == 0 ? 8 : 16) : 0;
     pp.op0 = h.op0;
@@ -1223,8 +1388,17 @@ static void finish_pass(Plan& p, PassPlan& pp, uint64_t upmask, bool dense)
     std::sort(pp.up.begin(), pp.up.end());
     pp.L = fixed + (int)pp.up.size();
     pp.bytes_alg = 2.0 * std::ldexp(1.0, n) * sz;
-    if (pp.type == PASS_TILE_LDS) emit_tile_lds(p, pp);
-    else emit_tile_reg(p, pp);
+}
+
+// Device programs of the packed tile passes, in execution order.
+static void emit_passes(Plan& p)
+{
+    Chain ch;
+    find_chains(p, ch);
+    for (PassPlan& pp : p.passes) {
+        if (pp.type == PASS_TILE_LDS) emit_tile_lds(p, pp);
+        else if (pp.type == PASS_TILE_REG) emit_tile_reg(p, pp, ch);
+    }
 }
 
 static void pack(Plan& p)
@@ -1420,6 +1594,7 @@ static void pack(Plan& p)
         }
     }
     flush();
+    emit_passes(p);
 }
 
 // Merging, fusion, packing and device-program emission of lowered

@@ -1,0 +1,83 @@
+"""Register tile passes with chains of 2x2 operations (the sheared forms):
+every coefficient type (complex, real, imaginary), pivots at and around the
+boundary between the plain and the exchanged form, register bits with
+exchanged slots under controls, phases, general diagonals, X and LDS remaps,
+and chains that end in a non-unitary 2x2.  Element by element against the
+oracle with the parity bounds of the other state tests (2e-5 / 1e-12)."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from workloads import circuits as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def q():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_09326_amd as qq
+    qq.lib()
+    return qq
+
+
+def chain_circuit(seed, n, layers, kinds):
+    """Per layer one 2x2 of a drawn kind on every qubit (angles at the pivot
+    boundary and its neighbours among them), then operations that read the
+    slot index: CZ, CP, RZZ, CX, a doubly controlled RY and an X."""
+    rng = np.random.default_rng(seed)
+    special = [0.0, np.pi / 2, np.nextafter(np.pi / 2, 4), np.nextafter(np.pi / 2, 0), np.pi, 3 * np.pi / 2]
+    g = []
+    for _ in range(layers):
+        for b in range(n):
+            kind = kinds[int(rng.integers(len(kinds)))]
+            th = special[int(rng.integers(6))] if rng.random() < 0.3 else float(rng.uniform(0, 2 * np.pi))
+            params = {"h": (), "sx": (), "u3": (th, *map(float, rng.uniform(0, 6.28, 2)))}.get(kind, (th,))
+            g.append(W.Gate(kind, (b,), (), params))
+        p = [int(v) for v in rng.permutation(n)]
+        g.append(W.Gate("cz", (p[0], p[1])))
+        g.append(W.Gate("cp", (p[2], p[3]), (), (0.7,)))
+        g.append(W.Gate("rzz", (p[4], p[5]), (), (1.1,)))
+        g.append(W.Gate("rzz", (p[5], p[6]), (), (0.3,)))
+        g.append(W.Gate("cx", (p[7], p[8])))
+        g.append(W.Gate("ry", (p[9],), (p[10], p[11]), (0.9,)))
+        g.append(W.Gate("x", (p[12],)))
+    return g
+
+
+@pytest.mark.parametrize("prec,tol", [(0, 2e-5), (1, 1e-12)])
+@pytest.mark.parametrize("tile_upper", [0, 4, 5, 6, 7])
+@pytest.mark.parametrize("kinds", [("u3",), ("ry", "h"), ("rx", "sx"), ("u3", "ry", "rx", "h", "rz")])
+def test_chains_match_oracle(q, prec, tol, tile_upper, kinds):
+    n = 14
+    c = W.Circuit(n, chain_circuit(len(kinds) + tile_upper, n, 5, kinds), x0=1234)
+    sim = q.Simulator(n, prec)
+    sim.init_basis(c.x0)
+    sim.run(q.Plan(n, c.gates, precision=prec, tile_upper=tile_upper))
+    got = sim.state().astype(np.complex128)
+    sim.close()
+    assert np.max(np.abs(got - orc.run_circuit(c))) <= tol
+
+
+@pytest.mark.parametrize("prec,tol", [(0, 2e-5), (1, 1e-12)])
+def test_chain_ends_in_a_singular_matrix(q, prec, tol):
+    """A projector (and a scaled 2x2) after unitary 2x2s on the same bits:
+    both absorb the waiting diagonal but start no chain of their own."""
+    n = 13
+    proj = np.array([[1.0, 0.0], [0.0, 0.0]], dtype=complex)
+    big = np.array([[0.3, 1.2j], [0.1, 2.0]], dtype=complex)
+    g = [W.Gate("u3", (b,), (), (0.3 + 0.2 * b, 1.0, 0.4)) for b in range(n)]
+    g += [W.Gate("cz", (b, b + 1)) for b in range(n - 1)]
+    g += [W.Gate("u3", (b,), (), (2.0 + 0.1 * b, 0.2, 0.9)) for b in range(n)]
+    g += [W.Gate("cz", (b, (b + 3) % n)) for b in range(n)]
+    g += [W.Gate("dense", (b,), (), (), proj if b in (2, 9) else big) for b in (2, 5, 9, 12)]
+    g += [W.Gate("cz", (0, 12)), W.Gate("ry", (5,), (), (0.4,)), W.Gate("ry", (12,), (), (0.8,))]
+    c = W.Circuit(n, g)
+    sim = q.Simulator(n, prec)
+    sim.init_basis(0)
+    sim.apply(c.gates)
+    got = sim.state().astype(np.complex128)
+    sim.close()
+    assert np.max(np.abs(got - orc.run_circuit(c))) <= tol
