@@ -1140,17 +1140,6 @@ hipError_t launch_init_basis(int prec, void* state, int n, uint64_t x, hipStream
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// FP64 reductions (fixed order, so results are bitwise reproducible)
-// ---------------------------------------------------------------------------
-
-template <typename V>
-__device__ __forceinline__ double prob(V v)
-{
-    const double re = (double)v.x, im = (double)v.y;
-    return re * re + im * im;
-}
-
 // Tree sum over the 256 threads of a block, fixed order.  `sh` has 256 doubles.
 __device__ __forceinline__ double block_sum_256(double v, double* sh)
 {
@@ -1165,336 +1154,9 @@ __device__ __forceinline__ double block_sum_256(double v, double* sh)
     return r;
 }
 
-// Block b sums the chunk [b 2^s, (b+1) 2^s): part[b*(n+1) + 0] = sum p,
-// part[b*(n+1) + 1 + q] = sum p * bit_q(x).  Bits 8..s-1 of x come from the
-// loop counter; LB >= s - 8 of them are tracked in registers.
-template <typename T, int LB>
-__global__ void __launch_bounds__(256)
-zsum_part_kernel(const typename CxT<T>::V* __restrict__ st, int n, int s, double* __restrict__ part)
-{
-    __shared__ double sh[256];
-    const uint64_t base = (uint64_t)blockIdx.x << s;
-    const uint32_t chunk = 1u << s;
-    const int t = threadIdx.x;
-    const int jb = s > 8 ? s - 8 : 0;           // bits 8..s-1 come from the loop counter
-    double tot = 0.0;
-    double sb[LB];
-#pragma unroll
-    for (int q = 0; q < LB; ++q) sb[q] = 0.0;
-    for (uint32_t j = 0; (j << 8) < chunk; ++j) {
-        const uint32_t off = (j << 8) + t;
-        if (off >= chunk) break;
-        const double p = prob(st[base + off]);
-        tot += p;
-#pragma unroll
-        for (int q = 0; q < LB; ++q)
-            if (q < jb && ((j >> q) & 1u)) sb[q] += p;
-    }
-    double* out = part + (uint64_t)blockIdx.x * (n + 1);
-    const double all = block_sum_256(tot, sh);
-    if (t == 0) out[0] = all;
-    for (int q = 0; q < n; ++q) {
-        double v;
-        if (q < 8 && q < s)
-            v = block_sum_256(((t >> q) & 1) ? tot : 0.0, sh);
-        else if (q < s) {
-            double mine = 0.0;
-#pragma unroll
-            for (int r = 0; r < LB; ++r)
-                if (r == q - 8) mine = sb[r];
-            v = block_sum_256(mine, sh);
-        }
-        else
-            v = ((base >> q) & 1ull) ? all : 0.0;
-        if (t == 0) out[1 + q] = v;
-    }
-}
-
-// One block per output quantity: sums part[b*(n+1) + qi] over blocks b.
-__global__ void __launch_bounds__(256) zsum_final_kernel(const double* __restrict__ part, int nparts, int n,
-                                                         double* __restrict__ out)
-{
-    __shared__ double sh[256];
-    const int qi = blockIdx.x;
-    double v = 0.0;
-    for (int b = threadIdx.x; b < nparts; b += 256) v += part[(uint64_t)b * (n + 1) + qi];
-    const double r = block_sum_256(v, sh);
-    if (threadIdx.x == 0) out[qi] = r;
-}
-
-static int zsum_chunk_bits(int n) { return n < 16 ? n : 16; }
-
-size_t zsum_scratch_doubles(int n)
-{
-    const int s = zsum_chunk_bits(n);
-    return (size_t(1) << (n - s)) * (n + 1);
-}
-
-template <typename T>
-static void launch_zsum_part(const void* state, int n, int s, double* part, hipStream_t st)
-{
-    using V = typename CxT<T>::V;
-    const unsigned nb = 1u << (n - s);
-    if (s <= 16)
-        hipLaunchKernelGGL((zsum_part_kernel<T, 8>), dim3(nb), dim3(256), 0, st, reinterpret_cast<const V*>(state), n,
-                           s, part);
-    else
-        hipLaunchKernelGGL((zsum_part_kernel<T, 16>), dim3(nb), dim3(256), 0, st, reinterpret_cast<const V*>(state),
-                           n, s, part);
-}
-
-static hipError_t launch_zsum_s(int prec, const void* state, int n, int s, double* part, double* out, hipStream_t st)
-{
-    if (prec == 0) launch_zsum_part<float>(state, n, s, part, st);
-    else launch_zsum_part<double>(state, n, s, part, st);
-    hipLaunchKernelGGL(zsum_final_kernel, dim3(n + 1), dim3(256), 0, st, part, (int)(1u << (n - s)), n, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_zsum(int prec, const void* state, int n, double* scratch, double* out, hipStream_t st)
-{
-    return launch_zsum_s(prec, state, n, zsum_chunk_bits(n), scratch, out, st);
-}
-
-// Chunks of 2^s amplitudes with s = max(zsum_chunk_bits(n), n - 11): at
-// most 2^11 partial records whatever n is (up to 24 chunk bits at n = 34);
-// for n <= 27 the chunks, and so the summation order, equal launch_zsum's.
-static int zsum_bounded_chunk_bits(int n) { return std::max(zsum_chunk_bits(n), n - 11); }
-
-size_t zsum_bounded_scratch_doubles(int n)
-{
-    return (size_t(1) << (n - zsum_bounded_chunk_bits(n))) * (n + 1) + (n + 1);
-}
-
-// out[q] = sums[0] - 2 sums[1 + l2p[q]]: <Z_q> of logical qubit q.
-__global__ void z_logical_kernel(const double* __restrict__ sums, int n, ZLayout lay, double* __restrict__ out)
-{
-    const int q = threadIdx.x;
-    if (q < n) out[q] = sums[0] - 2.0 * sums[1 + lay.l2p[q]];
-}
-
-hipError_t launch_expect_z_bounded(int prec, const void* state, int n, const int32_t* l2p, double* scratch,
-                                   double* out, hipStream_t st)
-{
-    if (n < 1 || n > QOPS_MAX_QUBITS_DEV) return hipErrorInvalidValue;
-    const int s = zsum_bounded_chunk_bits(n);
-    double* part = scratch;
-    double* sums = scratch + (size_t(1) << (n - s)) * (n + 1);
-    hipError_t e = launch_zsum_s(prec, state, n, s, part, sums, st);
-    if (e != hipSuccess) return e;
-    ZLayout lay;
-    for (int q = 0; q < QOPS_MAX_QUBITS_DEV; ++q) lay.l2p[q] = q < n ? l2p[q] : 0;
-    hipLaunchKernelGGL(z_logical_kernel, dim3(1), dim3(64), 0, st, sums, n, lay, out);
-    return hipGetLastError();
-}
-
-// Marginal probabilities.  Three paths:
-//  (a) m == n: a permutation of |psi|^2, no reduction;
-//  (b) at most 12 marginal bits: block b owns the chunk [b 2^s, (b+1) 2^s),
-//      reduces it sub-chunk by sub-chunk (4096 amplitudes) in LDS with a
-//      fixed summation order, and writes 2^(marginal bits below s) partials;
-//      a second kernel sums the partials over blocks in block order;
-//  (c) otherwise one thread per output y sums its 2^(n-m) terms in order.
-struct ProbGeom {
-    int s;          // chunk bits
-    int m_lo;       // marginal bits below s
-    int m12;        // marginal bits below 12
-    uint32_t lo_mask;  // physical mask of marginal bits below s
-};
-
-static ProbGeom prob_geom(int n, int m, const int* pos)
-{
-    ProbGeom g;
-    g.s = n < 20 ? n : 20;
-    g.m_lo = 0;
-    g.m12 = 0;
-    g.lo_mask = 0;
-    for (int j = 0; j < m; ++j) {
-        if (pos[j] < g.s) {
-            g.m_lo++;
-            g.lo_mask |= 1u << pos[j];
-        }
-        if (pos[j] < 12) g.m12++;
-    }
-    return g;
-}
-
 struct PosArr {
     int p[QOPS_MAX_QUBITS_DEV];
 };
-
-template <typename T>
-__global__ void __launch_bounds__(256)
-probs_direct_kernel(const typename CxT<T>::V* __restrict__ st, int n, PosArr pa, double* __restrict__ out)
-{
-    const uint64_t N = 1ull << n;
-    for (uint64_t x = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; x < N; x += (uint64_t)gridDim.x * blockDim.x) {
-        uint64_t y = 0;
-        for (int j = 0; j < n; ++j) y |= ((x >> pa.p[j]) & 1ull) << j;
-        out[y] = prob(st[x]);
-    }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256)
-probs_slow_kernel(const typename CxT<T>::V* __restrict__ st, int n, int m, PosArr pa, uint64_t pmask,
-                  double* __restrict__ out)
-{
-    const uint64_t ny = 1ull << m;
-    const uint64_t nz = 1ull << (n - m);
-    for (uint64_t y = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; y < ny; y += (uint64_t)gridDim.x * blockDim.x) {
-        uint64_t xy = 0;
-        for (int j = 0; j < m; ++j) xy |= ((y >> j) & 1ull) << pa.p[j];
-        double acc = 0.0;
-        for (uint64_t z = 0; z < nz; ++z) acc += prob(st[xy | spread_mask64(z, pmask)]);
-        out[y] = acc;
-    }
-}
-
-// y index of x restricted to the marginal bits selected by `sel` (a subset of
-// the m marginal bits, in j order), compressed.
-__device__ __forceinline__ uint32_t compress_sel(uint64_t x, const PosArr& pa, int m, uint32_t sel)
-{
-    uint32_t y = 0;
-    int o = 0;
-    for (int j = 0; j < m; ++j)
-        if (sel & (1u << j)) {
-            y |= (uint32_t)((x >> pa.p[j]) & 1ull) << o;
-            ++o;
-        }
-    return y;
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256)
-probs_part_kernel(const typename CxT<T>::V* __restrict__ st, int m, PosArr pa, int s, int m_lo,
-                  uint32_t sel_lo, uint32_t sel12, int m12, uint32_t mask12, double* __restrict__ part)
-{
-    __shared__ double tab[4096];
-    __shared__ double acc[4096];
-    const int t = threadIdx.x;
-    const uint64_t base = (uint64_t)blockIdx.x << s;
-    const uint32_t nacc = 1u << m_lo;
-    for (uint32_t i = t; i < nacc; i += 256) acc[i] = 0.0;
-    const int sub_bits = s < 12 ? s : 12;
-    const uint32_t sub = 1u << sub_bits;
-    const uint32_t nsub = 1u << (s - sub_bits);
-    const uint32_t n12 = 1u << m12;
-    const uint32_t nz = 1u << (sub_bits - m12);
-    __syncthreads();
-    for (uint32_t c = 0; c < nsub; ++c) {
-        const uint64_t sb = base + (uint64_t)c * sub;
-        for (uint32_t i = t; i < sub; i += 256) tab[i] = prob(st[sb + i]);
-        __syncthreads();
-        for (uint32_t y12 = t; y12 < n12; y12 += 256) {
-            // scatter y12 into the marginal bits below 12 (j order)
-            uint32_t xy = 0;
-            int o = 0;
-            for (int j = 0; j < m; ++j)
-                if (sel12 & (1u << j)) {
-                    xy |= ((y12 >> o) & 1u) << pa.p[j];
-                    ++o;
-                }
-            double v = 0.0;
-            for (uint32_t z = 0; z < nz; ++z) v += tab[xy | spread_mask(z, mask12)];
-            const uint32_t slot = compress_sel(sb | xy, pa, m, sel_lo);
-            acc[slot] += v;
-        }
-        __syncthreads();
-    }
-    for (uint32_t i = t; i < nacc; i += 256) part[(uint64_t)blockIdx.x * nacc + i] = acc[i];
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256)
-probs_reduce_kernel(const double* __restrict__ part, int n, int m, PosArr pa, int s, int m_lo, uint32_t sel_lo,
-                    uint64_t hi_mask_blocks, double* __restrict__ out)
-{
-    // hi_mask_blocks: bits of the block number that are marginal bits
-    const uint32_t ny = 1u << m;
-    const uint32_t nacc = 1u << m_lo;
-    const int nbb = n - s;
-    const uint64_t nfree = 1ull << (nbb - __popcll(hi_mask_blocks));
-    for (uint32_t y = blockIdx.x * blockDim.x + threadIdx.x; y < ny; y += gridDim.x * blockDim.x) {
-        uint32_t ylo = 0, o = 0;
-        uint64_t bfix = 0;
-        for (int j = 0; j < m; ++j) {
-            const uint32_t bit = (y >> j) & 1u;
-            if (sel_lo & (1u << j)) {
-                ylo |= bit << o;
-                ++o;
-            } else {
-                bfix |= (uint64_t)bit << (pa.p[j] - s);
-            }
-        }
-        double v = 0.0;
-        for (uint64_t f = 0; f < nfree; ++f) {
-            const uint64_t b = bfix | spread_mask64(f, hi_mask_blocks);
-            v += part[b * nacc + ylo];
-        }
-        out[y] = v;
-    }
-}
-
-size_t probs_scratch_doubles(int n, int m, const int* pos)
-{
-    if (m == n || m > 12) return 0;
-    const ProbGeom g = prob_geom(n, m, pos);
-    return (size_t(1) << (n - g.s)) * (size_t(1) << g.m_lo);
-}
-
-hipError_t launch_probs(int prec, const void* state, int n, int m, const int* pos, double* scratch, double* out,
-                        hipStream_t st)
-{
-    PosArr pa;
-    for (int j = 0; j < QOPS_MAX_QUBITS_DEV; ++j) pa.p[j] = j < m ? pos[j] : 0;
-    uint64_t pmask = 0;
-    for (int j = 0; j < m; ++j) pmask |= 1ull << pos[j];
-    if (m == n) {
-        const uint64_t N = 1ull << n;
-        if (prec == 0)
-            hipLaunchKernelGGL(probs_direct_kernel<float>, dim3(grid_for(N, 256)), dim3(256), 0, st,
-                               reinterpret_cast<const float2*>(state), n, pa, out);
-        else
-            hipLaunchKernelGGL(probs_direct_kernel<double>, dim3(grid_for(N, 256)), dim3(256), 0, st,
-                               reinterpret_cast<const double2*>(state), n, pa, out);
-        return hipGetLastError();
-    }
-    if (m > 12) {
-        const uint64_t ny = 1ull << m;
-        if (prec == 0)
-            hipLaunchKernelGGL(probs_slow_kernel<float>, dim3(grid_for(ny, 256)), dim3(256), 0, st,
-                               reinterpret_cast<const float2*>(state), n, m, pa, pmask, out);
-        else
-            hipLaunchKernelGGL(probs_slow_kernel<double>, dim3(grid_for(ny, 256)), dim3(256), 0, st,
-                               reinterpret_cast<const double2*>(state), n, m, pa, pmask, out);
-        return hipGetLastError();
-    }
-    const ProbGeom g = prob_geom(n, m, pos);
-    uint32_t sel_lo = 0, sel12 = 0, mask12 = 0;
-    uint64_t hi_blocks = 0;
-    for (int j = 0; j < m; ++j) {
-        if (pos[j] < g.s) sel_lo |= 1u << j;
-        else hi_blocks |= 1ull << (pos[j] - g.s);
-        if (pos[j] < 12 && pos[j] < g.s) {
-            sel12 |= 1u << j;
-            mask12 |= 1u << pos[j];
-        }
-    }
-    int m12 = __builtin_popcount(sel12);
-    const unsigned nb = 1u << (n - g.s);
-    if (prec == 0)
-        hipLaunchKernelGGL(probs_part_kernel<float>, dim3(nb), dim3(256), 0, st, reinterpret_cast<const float2*>(state),
-                           m, pa, g.s, g.m_lo, sel_lo, sel12, m12, mask12, scratch);
-    else
-        hipLaunchKernelGGL(probs_part_kernel<double>, dim3(nb), dim3(256), 0, st,
-                           reinterpret_cast<const double2*>(state), m, pa, g.s, g.m_lo, sel_lo, sel12, m12, mask12,
-                           scratch);
-    const uint64_t ny = 1ull << m;
-    hipLaunchKernelGGL(probs_reduce_kernel<float>, dim3(grid_for(ny, 256)), dim3(256), 0, st, scratch, n, m, pa, g.s,
-                       g.m_lo, sel_lo, hi_blocks, out);
-    return hipGetLastError();
-}
 
 // ---------------------------------------------------------------------------
 // Logical-order gather (readout through the layout map)

@@ -59,8 +59,8 @@ hipError_t launch_expect_z_bounded(int prec, const void* state, int n, const int
                                    double* out, hipStream_t s);
 
 // Marginal over physical bits pos[0..m-1] (host array); out: 2^m doubles
-// (device).  scratch must hold probs_scratch_doubles(n, m, pos) doubles.
-size_t probs_scratch_doubles(int n, int m, const int* pos);
+// (device).  scratch must hold probs_scratch_doubles(prec, n, m, pos) doubles.
+size_t probs_scratch_doubles(int prec, int n, int m, const int* pos);
 hipError_t launch_probs(int prec, const void* state, int n, int m, const int* pos, double* scratch,
                         double* out, hipStream_t s);
 

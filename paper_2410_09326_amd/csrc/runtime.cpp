@@ -609,7 +609,7 @@ int32_t qops_probabilities(qops_sim* h, const int32_t* qubits, int32_t m, double
             pos[j] = h->l2p[qubits[j]];
         }
         const size_t ny = size_t(1) << m;
-        const size_t part = probs_scratch_doubles(h->n, m, pos.data());
+        const size_t part = probs_scratch_doubles(h->prec, h->n, m, pos.data());
         int32_t rc = ensure_scratch(h, part + ny);
         if (rc) return rc;
         double* d_out = h->scratch + part;
