@@ -923,13 +923,33 @@ static void emit_lds_op(Plan& p, const LOp& o, int L, F tpos, PassPlan& pp, bool
 // of each such chain is applied in full.  `pend` holds the diagonal waiting on
 // each physical bit, with |d0 d1| = 1 at pass ends (the common factor moves to
 // the pass's store).  Everything is composed in FP64.
+// The composition runs in extended precision and rounds each coefficient once,
+// so that a chain's coefficients are as exact as single matrices'.
+struct Cl {
+    long double re = 0, im = 0;
+    Cl() = default;
+    Cl(long double r, long double i = 0) : re(r), im(i) {}
+    Cl(const cd& v) : re(v.real()), im(v.imag()) {}
+    cd to_cd() const { return cd((double)re, (double)im); }
+};
+static Cl operator*(const Cl& a, const Cl& b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
+static Cl operator-(const Cl& a, const Cl& b) { return {a.re - b.re, a.im - b.im}; }
+static Cl operator-(const Cl& a) { return {-a.re, -a.im}; }
+static long double norm2(const Cl& a) { return a.re * a.re + a.im * a.im; }
+static Cl operator/(const Cl& a, const Cl& b)
+{
+    const long double n = norm2(b);
+    return {(a.re * b.re + a.im * b.im) / n, (a.im * b.re - a.re * b.im) / n};
+}
+
 struct Chain {
     std::vector<char> shear;    // per lowered operation: a later 2x2 absorbs its diagonal
-    cd d0[64], d1[64];
-    double scale = 1.0;         // factor the current pass still owes
+    Cl d0[64], d1[64];
+    bool waits[64] = {false};
+    long double scale = 1.0;    // factor the current pass still owes
     Chain()
     {
-        for (int b = 0; b < 64; ++b) d0[b] = d1[b] = cd(1);
+        for (int b = 0; b < 64; ++b) d0[b] = d1[b] = Cl(1);
     }
 };
 
@@ -960,10 +980,10 @@ static void find_chains(const Plan& p, Chain& ch)
     }
 }
 
-static int coef_type(cd w, cd v)
+static int coef_type(const Cl& w, const Cl& v)
 {
-    if (w.imag() == 0.0 && v.imag() == 0.0) return 1;
-    if (w.real() == 0.0 && v.real() == 0.0) return 2;
+    if (w.im == 0 && v.im == 0) return 1;
+    if (w.re == 0 && v.re == 0) return 2;
     return 0;
 }
 
@@ -971,14 +991,19 @@ static int coef_type(cd w, cd v)
 // values (0, 1).  The pivot is the larger entry of the row, so |w|, |v| stay
 // near or below 1; of the two orders the one that keeps |d1/d0| nearer to 1
 // is taken, so the waiting diagonals stay within a factor of 2.
-static void shear_reg_form(const cd (&N)[4], int& form, int& flip, cd& w, cd& v, cd& d0, cd& d1)
+static void shear_reg_form(const Cl (&N)[4], int& form, int& flip, Cl& w, Cl& v, Cl& d0, Cl& d1)
 {
-    const cd det = N[0] * N[3] - N[1] * N[2];
-    const double c0 = std::norm(N[0]) + std::norm(N[2]), c1 = std::norm(N[1]) + std::norm(N[3]);
-    if (std::norm(N[0]) * c1 >= std::norm(N[1]) * c0) {
+    const Cl det = N[0] * N[3] - N[1] * N[2];
+    const long double c0 = norm2(N[0]) + norm2(N[2]), c1 = norm2(N[1]) + norm2(N[3]);
+    // how far |d1/d0| is from 1 with pivot x
+    auto ratio = [&](const Cl& x) {
+        const long double r = norm2(det) / (norm2(x) * norm2(x));
+        return r > 1 ? r : 1 / r;
+    };
+    if (norm2(N[0]) * c1 >= norm2(N[1]) * c0) {
         flip = 0;
-        const double ra = std::abs(std::log(std::abs(det / (N[0] * N[0]))));
-        const double rb = std::abs(std::log(std::abs(det / (N[3] * N[3]))));
+        const long double ra = ratio(N[0]);
+        const long double rb = ratio(N[3]);
         if (ra <= rb) {           // slot 0 first
             form = 0;
             d0 = N[0];
@@ -994,8 +1019,8 @@ static void shear_reg_form(const cd (&N)[4], int& form, int& flip, cd& w, cd& v,
         }
     } else {                      // slot 0 ends as bit value 1, slot 1 as 0
         flip = 1;
-        const double ra = std::abs(std::log(std::abs(det / (N[1] * N[1]))));
-        const double rb = std::abs(std::log(std::abs(det / (N[2] * N[2]))));
+        const long double ra = ratio(N[1]);
+        const long double rb = ratio(N[2]);
         if (ra <= rb) {           // slot 1 first
             form = 1;
             d0 = N[1];
@@ -1014,10 +1039,10 @@ static void shear_reg_form(const cd (&N)[4], int& form, int& flip, cd& w, cd& v,
 
 // Scaled form on a lane bit (no slots to exchange: the exchanged form takes
 // the partner's amplitude as its own).
-static void shear_lane_form(const cd (&N)[4], int& ex, cd& w, cd& v, cd& d0, cd& d1)
+static void shear_lane_form(const Cl (&N)[4], int& ex, Cl& w, Cl& v, Cl& d0, Cl& d1)
 {
-    const double c0 = std::norm(N[0]) + std::norm(N[2]), c1 = std::norm(N[1]) + std::norm(N[3]);
-    ex = std::norm(N[0]) * c1 >= std::norm(N[1]) * c0 ? 0 : 1;
+    const long double c0 = norm2(N[0]) + norm2(N[2]), c1 = norm2(N[1]) + norm2(N[3]);
+    ex = norm2(N[0]) * c1 >= norm2(N[1]) * c0 ? 0 : 1;
     d0 = ex ? N[1] : N[0];
     d1 = ex ? N[2] : N[3];
     w = (ex ? N[0] : N[1]) / d0;
@@ -1119,9 +1144,14 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
         if (o.kind == LOp::ONEQ && o.cmask == 0) {
             // the diagonal waiting on the bit joins the matrix
             const int b = o.t[0];
-            cd N[4] = {o.m[0] * ch.d0[b], o.m[1] * ch.d1[b], o.m[2] * ch.d0[b], o.m[3] * ch.d1[b]};
-            ch.d0[b] = ch.d1[b] = cd(1);
-            const bool is_x = N[0] == cd(0) && N[1] == cd(1) && N[2] == cd(1) && N[3] == cd(0);
+            const bool waits = ch.waits[b];
+            Cl N[4] = {o.m[0], o.m[1], o.m[2], o.m[3]};
+            if (waits) {
+                for (int e = 0; e < 4; ++e) N[e] = N[e] * ((e & 1) ? ch.d1[b] : ch.d0[b]);
+                ch.d0[b] = ch.d1[b] = Cl(1);
+                ch.waits[b] = false;
+            }
+            const bool is_x = !waits && o.m[0] == cd(0) && o.m[1] == cd(1) && o.m[2] == cd(1) && o.m[3] == cd(0);
             const bool lane = b < 6;
             const int rb = lane ? -1 : regbit(upos(b));
             if (!lane && (flip >> rb & 1u) && !is_x) {
@@ -1134,8 +1164,9 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
             else pp.n_reg_ops++;
             if (!is_x) pp.flops += 16.0 * std::ldexp(1.0, p.n);
             if (ch.shear[pp.lop[i]] && !is_x) {
-                cd w, v;
+                Cl w, v;
                 int form, fl = 0;
+                ch.waits[b] = true;
                 if (lane) {
                     d.type = OP_SHEAR_LANE;
                     shear_lane_form(N, form, w, v, ch.d0[b], ch.d1[b]);
@@ -1146,11 +1177,11 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
                 }
                 d.b = form;
                 d.c_lane = (uint32_t)coef_type(w, v);
-                d.coef = push_coef(p, {w, v, cd(0), cd(0)});   // as many as the full form
+                d.coef = push_coef(p, {w.to_cd(), v.to_cd(), cd(0), cd(0)});   // as many as the full form
             } else {
                 d.type = lane ? OP_1Q_LANE : OP_1Q_REG;
                 d.b = is_x ? 1 : 0;
-                d.coef = push_coef(p, {N[0], N[1], N[2], N[3]});
+                d.coef = push_coef(p, {N[0].to_cd(), N[1].to_cd(), N[2].to_cd(), N[3].to_cd()});
             }
         } else if (o.kind == LOp::ONEQ) {
             if (o.t[0] < 6) {
@@ -1205,13 +1236,14 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
     }
     // waiting diagonals keep |d0 d1| = 1; the rest is the store's factor
     for (int b = 0; b < p.n; ++b) {
-        const double g = std::sqrt(std::abs(ch.d0[b] * ch.d1[b]));
-        ch.d0[b] /= g;
-        ch.d1[b] /= g;
+        if (!ch.waits[b]) continue;
+        const long double g = std::sqrt(std::sqrt(norm2(ch.d0[b] * ch.d1[b])));
+        ch.d0[b] = {ch.d0[b].re / g, ch.d0[b].im / g};
+        ch.d1[b] = {ch.d1[b].re / g, ch.d1[b].im / g};
         ch.scale *= g;
     }
     h.flip = (int32_t)flip;
-    h.scale = ch.scale;
+    h.scale = (double)ch.scale;
     ch.scale = 1.0;
     h.nops = (int)p.dops.size() - h.op0;
     h.lds_bytes = W > 0 ? (1 << pp.L) * (p.prec == 0 ? 8 : 16) : 0;
