@@ -19,7 +19,7 @@ SOURCES = ["kernels.hip", "regtile.hip", "mlp.hip", "planner.cpp", "runtime.cpp"
 # The operation loop branches on wave-uniform values only; structurizing those
 # branches would pass the whole tile through merge blocks that copy it.
 REG_TILE_FLAGS = ["-mllvm", "-structurizecfg-skip-uniform-regions=true"]
-REG_TILES = [(t, r, w) for r in (5, 4) for t in ("double", "float") for w in (2, 1, 0)]
+REG_TILES = [(t, r, w) for r, ws in ((4, (3, 2, 0)), (3, (3, 2))) for t in ("double", "float") for w in ws]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -9,6 +9,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <memory>
@@ -72,10 +73,8 @@ int32_t plan_all(qops_batch_exec* e, const qops_batch* b)
         par.state_lds_max_n = e->small_max_n;
         par.max_fuse_k = e->fuse_k;
         par.L_lds = std::min(e->tile_bits, n);
-        // register tiles of the same width: up to 5 (complex64) / 4
-        // (complex128) register bits, the rest wave bits
-        par.R = b->precision == QOPS_C64 ? 5 : 4;
-        par.W = std::max(0, std::min(2, std::min(e->tile_bits, n) - 6 - par.R));
+        par.reg_up = std::min(e->tile_bits, n) - 6;   // register tiles of the same width
+        par.state_reg = 0;
         Err er = build_plan(n, b->precision, nullptr, b->gates[i], b->n_gates[i], par, e->plans[i]);
         if (!er.ok()) return set_error(er.code, "circuit " + std::to_string(i) + ": " + er.msg);
         const Plan& p = e->plans[i];
@@ -108,12 +107,18 @@ void program_images(const qops_batch_exec* e, std::vector<PassHdr>& hdrs, std::v
         const Plan& p = e->plans[i];
         const int op_base = (int)ops.size();
         const int32_t coef_n = (int32_t)e->coef_base[i];
-        for (DevOp d : p.dops) {
-            // LDS-tile ops with b = 1 address the pass's staged coefficients
-            const bool staged = d.b && (d.type == OP_MFMA || d.type == OP_DIAG_LDS || d.type == OP_DENSE_LDS);
-            d.coef += staged ? 0 : coef_n;
-            ops.push_back(d);
-        }
+        ops.insert(ops.end(), p.dops.begin(), p.dops.end());
+        for (const PassPlan& pp : p.passes)
+            for (int k = 0; k < pp.nops; ++k) {
+                DevOp& d = ops[op_base + pp.op0 + (size_t)k * pp.op_stride];
+                // register tile records: `coef` is at the same place; LDS
+                // tile ops with b = 1 address the pass's staged coefficients
+                static_assert(offsetof(DevOp, coef) == offsetof(RegOpT<float>, coef) &&
+                                  offsetof(DevOp, coef) == offsetof(RegOpT<double>, coef),
+                              "coefficient offset");
+                if (pp.type == PASS_TILE_LDS && d.b) continue;
+                d.coef += coef_n;
+            }
         if (p.n <= e->small_max_n) continue;
         for (const PassPlan& pp : p.passes) {
             PassHdr h = p.hdrs[pp.hdr];

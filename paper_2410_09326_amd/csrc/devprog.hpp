@@ -9,27 +9,10 @@ namespace qops {
 // Operation types inside a tile pass.
 enum OpType : int32_t {
     OP_NONE = 0,
-    OP_1Q_REG = 1,    // 2x2 on a register bit          a = register bit
-    OP_1Q_LANE = 2,   // 2x2 on a lane bit (shuffles)    a = lane bit (0..5)
-    OP_DIAG = 3,      // diagonal table over m bits      a = m, pos[i] = encoded source of bit i
-    OP_REMAP = 4,     // registers -> LDS -> registers   b = new mapping
     OP_DENSE_LDS = 7, // 2^k x 2^k on tile positions, vector ALU, in LDS   a = k, pos = tile positions
     OP_MFMA = 8,      // 2^k x 2^k on tile positions, matrix cores, in LDS  a = k, pos = tile positions
-    OP_DIAG_LDS = 9,  // diagonal table on tile positions, in LDS (whole-state kernel)
-    OP_CPHASE = 10,   // phase coef on amplitudes whose masked bits are all 1   b = 1: phase is -1
-    OP_SHEAR_REG = 11,   // sheared 2x2 on a register bit  a = register bit, b = form, c_lane = coefficient type
-    OP_SHEAR_LANE = 12   // scaled 2x2 on a lane bit       a = lane bit, b = 1: exchanged, c_lane = coefficient type
+    OP_DIAG_LDS = 9   // diagonal table on tile positions, in LDS (whole-state kernel)
 };
-// Register tile passes.  A 2x2 whose bit is next targeted by another
-// uncontrolled 2x2 runs in a two-coefficient form (coef: w, v; type 0 =
-// complex, 1 = real, 2 = imaginary) that leaves a diagonal factor on the bit,
-// and for register bits possibly exchanged slots; the planner folds the
-// factor into that next 2x2.  Register bits with exchanged slots ("flipped":
-// slot bit = 1 - bit) are resolved in the operations that read the slot
-// index: c_reg controls hold where slot & c_reg == c_tile (OP_1Q_*,
-// OP_CPHASE), OP_DIAG starts its table index at c_tile, OP_REMAP
-// carries the flipped register bits in c_reg, the store in PassHdr::flip.
-// OP_1Q_REG / OP_1Q_LANE: b = 1 marks an exact X (pure exchange, no arithmetic).
 // OP_MFMA / OP_DIAG_LDS / OP_DENSE_LDS in an LDS tile pass: b = 1 means `coef` is an offset
 // into the coefficients staged in LDS, b = 0 an offset into global memory.
 // OP_MFMA: c_reg (unused by LDS ops otherwise) holds QOPS_MFMA_WIDE when the
@@ -37,7 +20,7 @@ enum OpType : int32_t {
 // largest complex64 tile); its coefficients then follow that layout.
 #define QOPS_MFMA_WIDE 1u
 
-// Encoded source of one bit of a diagonal's table index (OP_DIAG pos[i]).
+// Encoded source of one bit of a diagonal's table index (RC_DIAG pos[i], OP_DIAG_LDS pos[i]).
 enum BitSrc : int32_t { SRC_LANE = 0, SRC_WAVE = 1, SRC_REG = 2, SRC_GLOB = 3 };
 __host__ __device__ inline int32_t enc_src(int32_t cls, int32_t v) { return (cls << 8) | v; }
 
@@ -46,14 +29,96 @@ struct DevOp {              // 64 bytes
     int32_t a;
     int32_t coef;           // offset of the coefficients in the coefficient array (scalar units)
     int32_t b;
-    uint32_t c_lane;        // controls on lane bits (tile positions 0..5)
-    uint32_t c_wave;        // controls on wave-id bits (current mapping)
-    uint32_t c_reg;         // controls on register-slot bits (current mapping)
-    uint32_t c_tile;        // controls on tile positions (LDS ops)
+    uint32_t c_lane;        // OP_MFMA: column positions (c_lane, c_wave)
+    uint32_t c_wave;
+    uint32_t c_reg;
+    uint32_t c_tile;        // controls on tile positions
     uint64_t c_glob;        // controls on physical bits outside the tile (checked per tile)
     int32_t pos[6];
 };
 static_assert(sizeof(DevOp) == 64, "DevOp layout");
+
+// Operations of register tile passes.  One flat code selects the unrolled
+// body (operation, register or lane bit, form, coefficient type), so the
+// kernel branches once per operation, and the record carries its own
+// coefficients, so the next one can be fetched as a whole while the current
+// one runs.  complex64 records take 64 bytes, complex128 ones 128 (the second
+// half of a full matrix in `more`); both live in the plan's DevOp array.
+//
+// A 2x2 whose bit is next targeted by another uncontrolled 2x2 runs in a
+// two-coefficient form (k: w, v) that leaves a diagonal factor on the bit, and
+// for register bits possibly exchanged slots; the planner folds the factor
+// into that next 2x2.  Register bits with exchanged slots ("flipped": slot bit
+// = 1 - bit) are resolved in the operations that read the slot index:
+// register controls hold where slot & c_reg == c_val, RC_DIAG starts its table
+// index at (aux >> 8) & 63, RC_REMAP carries the flipped register bits in c_reg, the
+// store in PassHdr::flip.
+//
+// A condition on register bits is uniform per slot, and testing it at run time
+// turns into compares and selects for every slot; so the common ones (one or
+// two register bits, each required 1 or 0) have bodies of their own, and only
+// the rest tests c_reg / c_val.  Pair (b, c), b < c, has number
+// c (c - 1) / 2 + b.
+enum RegCode : int32_t {
+    RC_NOP = 0,            // also pads the program by one record
+    RC_REMAP = 1,          // registers -> LDS -> registers        aux = new mapping
+    RC_X_LANE = 2,         // exact X on lane bit aux; + 1: controls outside the registers, + 2: any controls
+    RC_1Q_LANE = 5,        // full 2x2 on lane bit aux; + 1, + 2 as above
+    RC_X_REG = 8,          // + 3 register bit; + 1, + 2 as above
+    RC_1Q_REG = 23,        // + 3 register bit; + 1, + 2 as above
+    RC_SHEAR_REG = 38,     // + 6 register bit + 3 form + type (0 complex, 1 real, 2 imaginary)
+    RC_SHEAR_LANE = 68,    // + 6 lane bit + 3 exchanged + type
+    // diagonal tables, coef: table, pos: sources of its index bits; aux = m |
+    // first index << 8 | index bits of the register bits << 16 (3 bits each)
+    RC_DIAG = 104,         // any register bits
+    RC_DIAG0 = 105,        // none
+    RC_DIAG1 = 106,        // + register bit
+    RC_DIAG2 = 111,        // + pair number
+    // phase k[0] (sign: -1) where every masked bit is 1
+    RC_PHASE = 121,        // any register bits
+    RC_PHASE0 = 122,       // none
+    RC_PHASE1 = 123,       // + 2 register bit + required slot value
+    RC_PHASE2 = 133,       // + 4 pair number + required slot values (bit 0: lower register bit)
+    RC_SIGN = 173,         // as RC_PHASE
+    RC_SIGN0 = 174,
+    RC_SIGN1 = 175,
+    RC_SIGN2 = 185,
+    RC_CX_REG = 225,       // X on a register bit where another holds a value (no other control):
+                           // + 2 (2 pair number + (1: the target is the higher one)) + required value
+    RC_COUNT = 265
+};
+
+template <typename T>
+struct RegOpT;
+template <>
+struct RegOpT<float> {
+    int32_t code;
+    uint32_t ctl;           // c_lane | c_wave << 8 | c_reg << 16 | c_val << 24
+    int32_t coef;           // RC_DIAG: offset of the table in the coefficient array
+    int32_t aux;
+    uint64_t c_glob;        // controls on physical bits outside the tile (checked per tile)
+    union {
+        float k[8];
+        int32_t pos[6];
+    };
+    int32_t pad[2];
+};
+template <>
+struct RegOpT<double> {
+    int32_t code;
+    uint32_t ctl;
+    int32_t coef;
+    int32_t aux;
+    uint64_t c_glob;
+    union {
+        double k[4];
+        int32_t pos[6];
+    };
+    int64_t pad;
+    double more[4];         // k[4..7]
+    double pad2[4];
+};
+static_assert(sizeof(RegOpT<float>) == 64 && sizeof(RegOpT<double>) == 128, "RegOp layout");
 
 #define QOPS_MAX_UP 10
 // LDS tile passes hold physical bits 0..3 contiguously (128-byte runs of

@@ -36,7 +36,8 @@ struct PassPlan {
     std::vector<int> up;       // upper tile bits (physical)
     std::vector<int> lop;      // indices into Plan::lops
     int hdr = -1;              // index into Plan::hdrs (tile passes)
-    int op0 = 0, nops = 0;     // range in Plan::dops
+    int op0 = 0, nops = 0;     // operations in Plan::dops
+    int op_stride = 1;         // Plan::dops entries per operation (register tile passes of complex128: 2)
     int swap_a = 0, swap_b = 0;
     double bytes_alg = 0;      // algorithmic HBM bytes
     double flops = 0;
@@ -46,7 +47,8 @@ struct PassPlan {
 struct PlanParams {
     int mode = QOPS_PLAN_FUSED;
     int swap_mode = QOPS_SWAP_VIRTUAL;
-    int R = 5, W = 2;          // register-tile variant
+    int reg_up = 0;            // upper bits of register tiles (0 = by state size)
+    int state_reg = 1;         // small states without dense blocks run as one register tile
     int L_lds = 13;            // LDS-tile bits
     int max_fuse_k = 1;
     int use_mfma = 1;
@@ -69,6 +71,7 @@ struct Plan {
     std::vector<PassHdr> hdrs;
     std::vector<DevOp> dops;
     std::vector<double> coef;          // FP64 image; cast to the state precision at upload
+    int reg_upper = 0;                 // upper bits of the plan's register tiles
     int n_virtual_swaps = 0;
     int n_folded = 0;                  // phase gates removed by rotation folding
     double plan_seconds = 0;

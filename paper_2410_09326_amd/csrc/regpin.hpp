@@ -11,25 +11,29 @@
 
 namespace qops {
 
-using F32x32 = float __attribute__((ext_vector_type(32)));
-using F64x16 = double __attribute__((ext_vector_type(16)));
+template <typename T, int N>
+struct Tuple {
+    using V = T __attribute__((ext_vector_type(N)));
+};
 
+// Amplitudes per tuple: 32 registers at most.
 template <int N>
 __device__ __forceinline__ void pin_tile(float2 (&a)[N])
 {
+    constexpr int M = N < 16 ? N : 16;
 #pragma unroll
-    for (int h = 0; h < N / 16; ++h) {
-        F32x32 v;
+    for (int h = 0; h < N / M; ++h) {
+        typename Tuple<float, 2 * M>::V v;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            v[2 * j] = a[16 * h + j].x;
-            v[2 * j + 1] = a[16 * h + j].y;
+        for (int j = 0; j < M; ++j) {
+            v[2 * j] = a[M * h + j].x;
+            v[2 * j + 1] = a[M * h + j].y;
         }
         asm volatile("" : "+v"(v));
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            a[16 * h + j].x = v[2 * j];
-            a[16 * h + j].y = v[2 * j + 1];
+        for (int j = 0; j < M; ++j) {
+            a[M * h + j].x = v[2 * j];
+            a[M * h + j].y = v[2 * j + 1];
         }
     }
 }
@@ -37,19 +41,20 @@ __device__ __forceinline__ void pin_tile(float2 (&a)[N])
 template <int N>
 __device__ __forceinline__ void pin_tile(double2 (&a)[N])
 {
+    constexpr int M = N < 8 ? N : 8;
 #pragma unroll
-    for (int h = 0; h < N / 8; ++h) {
-        F64x16 v;
+    for (int h = 0; h < N / M; ++h) {
+        typename Tuple<double, 2 * M>::V v;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            v[2 * j] = a[8 * h + j].x;
-            v[2 * j + 1] = a[8 * h + j].y;
+        for (int j = 0; j < M; ++j) {
+            v[2 * j] = a[M * h + j].x;
+            v[2 * j + 1] = a[M * h + j].y;
         }
         asm volatile("" : "+v"(v));
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            a[8 * h + j].x = v[2 * j];
-            a[8 * h + j].y = v[2 * j + 1];
+        for (int j = 0; j < M; ++j) {
+            a[M * h + j].x = v[2 * j];
+            a[M * h + j].y = v[2 * j + 1];
         }
     }
 }

@@ -36,6 +36,19 @@ __device__ __forceinline__ void swap_reg(double& x, double& y)
     x = __builtin_bit_cast(double, a);
     y = __builtin_bit_cast(double, b);
 }
+// Exchange where mask is all ones (bits only, so the values are untouched).
+__device__ __forceinline__ void swap_masked(float& x, float& y, int mask)
+{
+    const int a = __float_as_int(x), b = __float_as_int(y), d = (a ^ b) & mask;
+    x = __int_as_float(a ^ d);
+    y = __int_as_float(b ^ d);
+}
+__device__ __forceinline__ void swap_masked(double& x, double& y, int mask)
+{
+    const long long a = __double_as_longlong(x), b = __double_as_longlong(y), d = (a ^ b) & (long long)mask;
+    x = __longlong_as_double(a ^ d);
+    y = __longlong_as_double(b ^ d);
+}
 __device__ __forceinline__ void put_reg(float2& d, const float2 v)
 {
     asm("v_mov_b32 %0, %1" : "=v"(d.x) : "v"(v.x));
@@ -47,8 +60,29 @@ __device__ __forceinline__ void put_reg(double2& d, const double2 v)
     asm("v_mov_b64 %0, %1" : "=v"(d.y) : "v"(v.y));
 }
 
-__device__ __forceinline__ void put_one(float& d, float v) { asm("v_mov_b32 %0, %1" : "=v"(d) : "v"(v)); }
-__device__ __forceinline__ void put_one(double& d, double v) { asm("v_mov_b64 %0, %1" : "=v"(d) : "v"(v)); }
+// Steps that have to end in the amplitude's own registers, in an order in which
+// no old value is needed after its register is overwritten.
+#define QOPS_IN_PLACE(T, FMA, MOV)                                                                           \
+    /* a = a b given t = a.y b.y, u = a.y b.x */                                                             \
+    __device__ __forceinline__ void cmul_tail(T& ax, T& ay, T bx, T by, T t, T u)                            \
+    {                                                                                                        \
+        asm(FMA " %1, %0, %3, %5\n\t" FMA " %0, %0, %2, -%4" : "+v"(ax), "=&v"(ay) : "v"(bx), "v"(by), "v"(t), "v"(u)); \
+    }                                                                                                        \
+    /* a = t + i c a.y, u + c' a.y: ax = t - ci ay, ay = u + cr ay */                                         \
+    __device__ __forceinline__ void ex_tail(T& ax, T& ay, T cr, T ci, T t, T u)                              \
+    {                                                                                                        \
+        asm(FMA " %0, -%2, %1, %4\n\t" FMA " %1, %3, %1, %5" : "=&v"(ax), "+v"(ay) : "v"(ci), "v"(cr), "v"(t), "v"(u)); \
+    }                                                                                                        \
+    /* x = p + c x */                                                                                        \
+    __device__ __forceinline__ void ex_real(T& x, T c, T p) { asm(FMA " %0, %1, %0, %2" : "+v"(x) : "v"(c), "v"(p)); } \
+    /* ax = p - ci ay, ay = u */                                                                             \
+    __device__ __forceinline__ void ex_imag(T& ax, T& ay, T ci, T p, T u)                                    \
+    {                                                                                                        \
+        asm(FMA " %0, -%2, %1, %3\n\t" MOV " %1, %4" : "=&v"(ax), "+v"(ay) : "v"(ci), "v"(p), "v"(u));       \
+    }
+QOPS_IN_PLACE(float, "v_fma_f32", "v_mov_b32")
+QOPS_IN_PLACE(double, "v_fma_f64", "v_mov_b64")
+#undef QOPS_IN_PLACE
 
 // a *= b (complex), in place.
 template <typename V>
@@ -56,26 +90,26 @@ __device__ __forceinline__ void cmul_to(V& a, const V b)
 {
     const auto t = a.y * b.y;
     const auto u = a.y * b.x;
-    a.y = fmat(a.x, b.y, u);
-    a.x = fmat(a.x, b.x, -t);
+    cmul_tail(a.x, a.y, b.x, b.y, t, u);
 }
 
 // 2x2 on register bit B.  Register-slot controls (slots whose bits `creg`
 // equal `cval`) are compile-time per slot and uniform; `tok` is the per-lane
 // control result.
 // Exact X on register bit B: exchange the two halves (no arithmetic).
-template <int B, int R, bool CTRL, typename V>
+// CTRL: 0 = none, 1 = controls outside the registers (`tok`), 2 = any.
+template <int B, int R, int CTRL, typename V>
 __device__ __forceinline__ void xgate_reg_b(V (&a)[1 << R], uint32_t creg, uint32_t cval, bool tok)
 {
+    const int mask = tok ? -1 : 0;
     sfor<(1 << R)>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
         if constexpr (!(j & (1 << B))) {
             constexpr int j1 = j | (1 << B);
-            if (!CTRL || ((uint32_t)j & creg) == cval) {
-                const V x0 = a[j], x1 = a[j1];
+            if (CTRL < 2 || ((uint32_t)j & creg) == cval) {
                 if (CTRL) {
-                    a[j] = csel(tok, x1, x0);
-                    a[j1] = csel(tok, x0, x1);
+                    swap_masked(a[j].x, a[j1].x, mask);
+                    swap_masked(a[j].y, a[j1].y, mask);
                 } else {
                     swap_reg(a[j].x, a[j1].x);
                     swap_reg(a[j].y, a[j1].y);
@@ -86,34 +120,21 @@ __device__ __forceinline__ void xgate_reg_b(V (&a)[1 << R], uint32_t creg, uint3
     pin_tile(a);
 }
 
-template <int R, bool CTRL, typename V>
-__device__ __forceinline__ void xgate_reg(int b, V (&a)[1 << R], uint32_t creg, uint32_t cval, bool tok)
-{
-    switch (b) {
-    case 0: xgate_reg_b<0, R, CTRL>(a, creg, cval, tok); break;
-    case 1: if constexpr (R > 1) xgate_reg_b<1, R, CTRL>(a, creg, cval, tok); break;
-    case 2: if constexpr (R > 2) xgate_reg_b<2, R, CTRL>(a, creg, cval, tok); break;
-    case 3: if constexpr (R > 3) xgate_reg_b<3, R, CTRL>(a, creg, cval, tok); break;
-    case 4: if constexpr (R > 4) xgate_reg_b<4, R, CTRL>(a, creg, cval, tok); break;
-    case 5: if constexpr (R > 5) xgate_reg_b<5, R, CTRL>(a, creg, cval, tok); break;
-    default: __builtin_unreachable();
-    }
-}
-
-template <int B, int R, bool CTRL, typename V>
+template <int B, int R, int CTRL, typename V>
 __device__ __forceinline__ void oneq_reg_b(V (&a)[1 << R], V m00, V m01, V m10, V m11, uint32_t creg, uint32_t cval, bool tok)
 {
     sfor<(1 << R)>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
         if constexpr (!(j & (1 << B))) {
             constexpr int j1 = j | (1 << B);
-            if (!CTRL || ((uint32_t)j & creg) == cval) {
+            if (CTRL < 2 || ((uint32_t)j & creg) == cval) {
                 const V x0 = a[j], x1 = a[j1];
                 const V y0 = cdot2(m00, x0, m01, x1);
                 const V y1 = cdot2(m10, x0, m11, x1);
                 if (CTRL) {
-                    a[j] = csel(tok, y0, x0);
-                    a[j1] = csel(tok, y1, x1);
+                    const V t = csel(tok, y0, x0), u = csel(tok, y1, x1);
+                    put_reg(a[j], t);
+                    put_reg(a[j1], u);
                 } else {
                     put_reg(a[j], y0);
                     put_reg(a[j1], y1);
@@ -124,18 +145,64 @@ __device__ __forceinline__ void oneq_reg_b(V (&a)[1 << R], V m00, V m01, V m10, 
     pin_tile(a);
 }
 
-template <int R, bool CTRL, typename V>
-__device__ __forceinline__ void oneq_reg(int b, V (&a)[1 << R], V m00, V m01, V m10, V m11, uint32_t creg, uint32_t cval, bool tok)
+// Bodies whose register condition is known at compile time: slots whose bits
+// in M equal VAL.
+template <int R, uint32_t M, uint32_t VAL, typename T, typename V>
+__device__ __forceinline__ void sign_slots(V (&a)[1 << R], T sgn)
 {
-    switch (b) {
-    case 0: oneq_reg_b<0, R, CTRL>(a, m00, m01, m10, m11, creg, cval, tok); break;
-    case 1: if constexpr (R > 1) oneq_reg_b<1, R, CTRL>(a, m00, m01, m10, m11, creg, cval, tok); break;
-    case 2: if constexpr (R > 2) oneq_reg_b<2, R, CTRL>(a, m00, m01, m10, m11, creg, cval, tok); break;
-    case 3: if constexpr (R > 3) oneq_reg_b<3, R, CTRL>(a, m00, m01, m10, m11, creg, cval, tok); break;
-    case 4: if constexpr (R > 4) oneq_reg_b<4, R, CTRL>(a, m00, m01, m10, m11, creg, cval, tok); break;
-    case 5: if constexpr (R > 5) oneq_reg_b<5, R, CTRL>(a, m00, m01, m10, m11, creg, cval, tok); break;
-    default: __builtin_unreachable();
+    sfor<(1 << R)>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        if constexpr (((uint32_t)j & M) == VAL) {
+            a[j].x *= sgn;
+            a[j].y *= sgn;
+        }
+    });
+    pin_tile(a);
+}
+
+template <int R, uint32_t M, uint32_t VAL, typename V>
+__device__ __forceinline__ void phase_slots(V (&a)[1 << R], const V ph)
+{
+    sfor<(1 << R)>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        if constexpr (((uint32_t)j & M) == VAL) cmul_to(a[j], ph);
+    });
+    pin_tile(a);
+}
+
+// Diagonal table with one or two register bits MA, MB (0: none) at the table
+// index bits named in `aux`.
+template <typename T, int R, uint32_t MA, uint32_t MB, typename V>
+__device__ __forceinline__ void diag_regs(V (&a)[1 << R], const T* __restrict__ tab, uint32_t ithr, int aux)
+{
+    const uint32_t ia = 1u << (aux >> 16 & 7), ib = MB ? 1u << (aux >> 19 & 7) : 0u;
+    const V p0 = ldc(tab, (int)ithr), p1 = ldc(tab, (int)(ithr ^ ia));
+    V p2 = p0, p3 = p1;
+    if constexpr (MB != 0u) {
+        p2 = ldc(tab, (int)(ithr ^ ib));
+        p3 = ldc(tab, (int)(ithr ^ ia ^ ib));
     }
+    sfor<(1 << R)>([&](auto jc) {
+        constexpr uint32_t j = decltype(jc)::value;
+        if constexpr ((j & MA) && (j & MB)) cmul_to(a[j], p3);
+        else if constexpr ((j & MB) != 0u) cmul_to(a[j], p2);
+        else if constexpr ((j & MA) != 0u) cmul_to(a[j], p1);
+        else cmul_to(a[j], p0);
+    });
+    pin_tile(a);
+}
+
+template <int B, int R, uint32_t M, uint32_t VAL, typename V>
+__device__ __forceinline__ void cx_slots(V (&a)[1 << R])
+{
+    sfor<(1 << R)>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        if constexpr (!(j & (1 << B)) && ((uint32_t)j & M) == VAL) {
+            swap_reg(a[j].x, a[j | (1 << B)].x);
+            swap_reg(a[j].y, a[j | (1 << B)].y);
+        }
+    });
+    pin_tile(a);
 }
 
 // Two-step (sheared) form of a 2x2 on register bit B: p += w q, then
@@ -177,20 +244,6 @@ __device__ __forceinline__ void shear_reg_b(V (&a)[1 << R], T wr, T wi, T vr, T 
     pin_tile(a);
 }
 
-template <int R, int FORM, int TY, typename T, typename V>
-__device__ __forceinline__ void shear_reg(int b, V (&a)[1 << R], T wr, T wi, T vr, T vi)
-{
-    switch (b) {
-    case 0: shear_reg_b<0, R, FORM, TY>(a, wr, wi, vr, vi); break;
-    case 1: if constexpr (R > 1) shear_reg_b<1, R, FORM, TY>(a, wr, wi, vr, vi); break;
-    case 2: if constexpr (R > 2) shear_reg_b<2, R, FORM, TY>(a, wr, wi, vr, vi); break;
-    case 3: if constexpr (R > 3) shear_reg_b<3, R, FORM, TY>(a, wr, wi, vr, vi); break;
-    case 4: if constexpr (R > 4) shear_reg_b<4, R, FORM, TY>(a, wr, wi, vr, vi); break;
-    case 5: if constexpr (R > 5) shear_reg_b<5, R, FORM, TY>(a, wr, wi, vr, vi); break;
-    default: __builtin_unreachable();
-    }
-}
-
 // Cross-lane exchange through ds_bpermute; `addr` = 4 * (lane ^ mask).
 __device__ __forceinline__ float shfl_xor_f(float v, int addr)
 {
@@ -205,13 +258,13 @@ __device__ __forceinline__ double shfl_xor_f(double v, int addr)
 }
 
 // Exact X on lane bit t: take the partner's amplitude.
-template <int R, bool CTRL, typename V>
+template <int R, int CTRL, typename V>
 __device__ __forceinline__ void xgate_lane(int t, int lane, V (&a)[1 << R], uint32_t creg, uint32_t cval, bool tok)
 {
     const int addr = (lane ^ (1 << t)) << 2;
     sfor<(1 << R)>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
-        if (!CTRL || ((uint32_t)j & creg) == cval) {
+        if (CTRL < 2 || ((uint32_t)j & creg) == cval) {
             V p;
             p.x = shfl_xor_f(a[j].x, addr);
             p.y = shfl_xor_f(a[j].y, addr);
@@ -223,7 +276,7 @@ __device__ __forceinline__ void xgate_lane(int t, int lane, V (&a)[1 << R], uint
 
 // 2x2 on lane bit t: each lane computes its own output from its amplitude
 // and its partner's (lane ^ 2^t).
-template <int R, bool CTRL, typename V>
+template <int R, int CTRL, typename V>
 __device__ __forceinline__ void oneq_lane(int t, int lane, V (&a)[1 << R], V m00, V m01, V m10, V m11,
                                           uint32_t creg, uint32_t cval, bool tok)
 {
@@ -233,15 +286,12 @@ __device__ __forceinline__ void oneq_lane(int t, int lane, V (&a)[1 << R], V m00
     const int addr = (lane ^ (1 << t)) << 2;
     sfor<(1 << R)>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
-        if (!CTRL || ((uint32_t)j & creg) == cval) {
+        if (CTRL < 2 || ((uint32_t)j & creg) == cval) {
             V p;
             p.x = shfl_xor_f(a[j].x, addr);
             p.y = shfl_xor_f(a[j].y, addr);
             const V y = cdot2(ms, a[j], mo, p);
-            if (CTRL)
-                a[j] = csel(tok, y, a[j]);
-            else
-                put_reg(a[j], y);
+            put_reg(a[j], CTRL ? csel(tok, y, a[j]) : y);
         }
     });
     pin_tile(a);
@@ -290,34 +340,18 @@ __device__ __forceinline__ void shear_lane_b(int lane, V (&a)[1 << R], T wr, T w
         if constexpr (EX && TY == 0) {
             // p + c a into a: both products with a.x before a.x is replaced
             const T t = fmat(cr, a[j].x, p.x), u = fmat(ci, a[j].x, p.y);
-            a[j].x = fmat(-ci, a[j].y, t);
-            a[j].y = fmat(cr, a[j].y, u);
+            ex_tail(a[j].x, a[j].y, cr, ci, t, u);
         } else if constexpr (EX && TY == 1) {
-            a[j].x = fmat(cr, a[j].x, p.x);
-            a[j].y = fmat(cr, a[j].y, p.y);
+            ex_real(a[j].x, cr, p.x);
+            ex_real(a[j].y, cr, p.y);
         } else if constexpr (EX) {
             const T u = fmat(ci, a[j].x, p.y);
-            a[j].x = fmat(-ci, a[j].y, p.x);
-            put_one(a[j].y, u);
+            ex_imag(a[j].x, a[j].y, ci, p.x, u);
         } else {
             axpy<TY>(a[j], cr, ci, p);
         }
     });
     pin_tile(a);
-}
-
-template <int R, bool EX, int TY, typename T, typename V>
-__device__ __forceinline__ void shear_lane(int t, int lane, V (&a)[1 << R], T wr, T wi, T vr, T vi)
-{
-    switch (t) {
-    case 0: shear_lane_b<0, R, EX, TY>(lane, a, wr, wi, vr, vi); break;
-    case 1: shear_lane_b<1, R, EX, TY>(lane, a, wr, wi, vr, vi); break;
-    case 2: shear_lane_b<2, R, EX, TY>(lane, a, wr, wi, vr, vi); break;
-    case 3: shear_lane_b<3, R, EX, TY>(lane, a, wr, wi, vr, vi); break;
-    case 4: shear_lane_b<4, R, EX, TY>(lane, a, wr, wi, vr, vi); break;
-    case 5: shear_lane_b<5, R, EX, TY>(lane, a, wr, wi, vr, vi); break;
-    default: __builtin_unreachable();
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -407,7 +441,7 @@ __device__ __forceinline__ void reg_tile(typename CxT<T>::V* __restrict__ st, co
     using V = typename CxT<T>::V;
     constexpr int NR = 1 << R;
     const int nops = hp->nops;
-    const DevOp* __restrict__ prog = ops + hp->op0;
+    const RegOpT<T>* __restrict__ prog = reinterpret_cast<const RegOpT<T>*>(ops + hp->op0);
     const int nruns = hp->nruns;
     const int32_t* __restrict__ up_phys = hp->up_phys;
     {
@@ -430,158 +464,154 @@ __device__ __forceinline__ void reg_tile(typename CxT<T>::V* __restrict__ st, co
             const V* src = st + base + ms.tphys;
             sfor<NR>([&](auto jc) { a[decltype(jc)::value] = src[reg_phys(ms, decltype(jc)::value)]; });
         }
+        // the next record is fetched while the current one runs (the program
+        // ends with a pad record)
+        RegOpT<T> next = prog[0];
         for (int i = 0; i < nops; ++i) {
             pin_tile(a);
-            const DevOp op = prog[i];
+            const RegOpT<T> op = next;
+            next = prog[i + 1];
             if ((base & op.c_glob) != op.c_glob) continue;   // tile-uniform control
-            switch (op.type) {
-            case OP_SHEAR_REG: {
-                const T* c = coef + op.coef;
-                const T wr = c[0], wi = c[1], vr = c[2], vi = c[3];
-                if (op.b == 0) {
-                    if (op.c_lane == 0) shear_reg<R, 0, 0>(op.a, a, wr, wi, vr, vi);
-                    else if (op.c_lane == 1) shear_reg<R, 0, 1>(op.a, a, wr, wi, vr, vi);
-                    else shear_reg<R, 0, 2>(op.a, a, wr, wi, vr, vi);
-                } else {
-                    if (op.c_lane == 0) shear_reg<R, 1, 0>(op.a, a, wr, wi, vr, vi);
-                    else if (op.c_lane == 1) shear_reg<R, 1, 1>(op.a, a, wr, wi, vr, vi);
-                    else shear_reg<R, 1, 2>(op.a, a, wr, wi, vr, vi);
-                }
-                break;
-            }
-            case OP_SHEAR_LANE: {
-                const T* c = coef + op.coef;
-                const T wr = c[0], wi = c[1], vr = c[2], vi = c[3];
-                if (op.b == 0) {
-                    if (op.c_lane == 0) shear_lane<R, false, 0>(op.a, lane, a, wr, wi, vr, vi);
-                    else if (op.c_lane == 1) shear_lane<R, false, 1>(op.a, lane, a, wr, wi, vr, vi);
-                    else shear_lane<R, false, 2>(op.a, lane, a, wr, wi, vr, vi);
-                } else {
-                    if (op.c_lane == 0) shear_lane<R, true, 0>(op.a, lane, a, wr, wi, vr, vi);
-                    else if (op.c_lane == 1) shear_lane<R, true, 1>(op.a, lane, a, wr, wi, vr, vi);
-                    else shear_lane<R, true, 2>(op.a, lane, a, wr, wi, vr, vi);
-                }
-                break;
-            }
-            case OP_1Q_REG:
-            case OP_1Q_LANE: {
-                const T* c = coef + op.coef;
-                const V m00 = ldc(c, 0), m01 = ldc(c, 1), m10 = ldc(c, 2), m11 = ldc(c, 3);
-                const bool ctrl = (op.c_lane | op.c_wave | op.c_reg) != 0;
-                const bool tok = ((uint32_t)lane & op.c_lane) == op.c_lane && ((uint32_t)wave & op.c_wave) == op.c_wave;
-                if (op.b == 1) {   // exact X: exchange only
-                    if (op.type == OP_1Q_REG) {
-                        if (ctrl) xgate_reg<R, true>(op.a, a, op.c_reg, op.c_tile, tok);
-                        else xgate_reg<R, false>(op.a, a, 0u, 0u, true);
-                    } else {
-                        if (ctrl) xgate_lane<R, true>(op.a, lane, a, op.c_reg, op.c_tile, tok);
-                        else xgate_lane<R, false>(op.a, lane, a, 0u, 0u, true);
-                    }
-                } else if (op.type == OP_1Q_REG) {
-                    if (ctrl)
-                        oneq_reg<R, true>(op.a, a, m00, m01, m10, m11, op.c_reg, op.c_tile, tok);
-                    else
-                        oneq_reg<R, false>(op.a, a, m00, m01, m10, m11, 0u, 0u, true);
-                } else {
-                    if (ctrl)
-                        oneq_lane<R, true>(op.a, lane, a, m00, m01, m10, m11, op.c_reg, op.c_tile, tok);
-                    else
-                        oneq_lane<R, false>(op.a, lane, a, m00, m01, m10, m11, 0u, 0u, true);
-                }
-                break;
-            }
-            case OP_CPHASE: {
-                // phase on the amplitudes whose masked bits are all 1; the
-                // register part of the condition is uniform per slot
-                const bool tok = ((uint32_t)lane & op.c_lane) == op.c_lane && ((uint32_t)wave & op.c_wave) == op.c_wave;
-                const bool thr = (op.c_lane | op.c_wave) != 0;
-                const uint32_t creg = op.c_reg, cval = op.c_tile;
-                // the multiplier is 1 where the lane's bits do not match
-                V ph = ldc(coef + op.coef, 0);
-                if (thr) {
-                    ph.x = tok ? ph.x : (T)1;
-                    ph.y = tok ? ph.y : (T)0;
-                }
-                if (op.b == 1) {   // -1: flip signs (lanes that do not match multiply by +1)
-                    const T sgn = ph.x;
-                    sfor<NR>([&](auto jc) {
-                        constexpr int j = decltype(jc)::value;
-                        if (((uint32_t)j & creg) == cval) {
-                            a[j].x *= sgn;
-                            a[j].y *= sgn;
-                        }
-                    });
-                } else {
-                    sfor<NR>([&](auto jc) {
-                        constexpr int j = decltype(jc)::value;
-                        if (((uint32_t)j & creg) == cval) cmul_to(a[j], ph);
-                    });
-                }
-                pin_tile(a);
-                break;
-            }
-            case OP_DIAG: {
-                const T* tab = coef + op.coef;
-                const int m = op.a;
-                uint32_t ithr = op.c_tile;   // table bits on flipped register bits start at 1
-                uint32_t rm[6];
+            const uint32_t c_lane = op.ctl & 255u, c_wave = (op.ctl >> 8) & 255u, creg = (op.ctl >> 16) & 255u,
+                           cval = op.ctl >> 24;
+            auto tok_of = [&]() {
+                return ((uint32_t)lane & c_lane) == c_lane && ((uint32_t)wave & c_wave) == c_wave;
+            };
+            auto sign_of = [&]() { return tok_of() ? (T)-1 : (T)1; };   // lanes that do not match: +1
+            auto phase_of = [&]() {
+                const bool tok = tok_of();
+                V ph;
+                ph.x = tok ? op.k[0] : (T)1;
+                ph.y = tok ? op.k[1] : (T)0;
+                return ph;
+            };
+            auto tab_of = [&]() { return coef + op.coef; };
+            // table index of the bits outside the registers (flipped register bits start at 1)
+            auto ithr_of = [&]() {
+                uint32_t idx = (uint32_t)op.aux >> 8 & 63u;
 #pragma unroll
                 for (int q = 0; q < 6; ++q) {
-                    rm[q] = 0;
-                    if (q < m) {
-                        const int cls = op.pos[q] >> 8, v = op.pos[q] & 255;
-                        if (cls == SRC_LANE) ithr |= (uint32_t)((lane >> v) & 1) << q;
-                        else if (cls == SRC_WAVE) ithr |= (uint32_t)((wave >> v) & 1) << q;
-                        else if (cls == SRC_GLOB) ithr |= (uint32_t)((base >> v) & 1ull) << q;
-                        else rm[q] = 1u << v;
-                    }
+                    if (q >= (op.aux & 255)) break;
+                    const int cls = op.pos[q] >> 8, v = op.pos[q] & 255;
+                    if (cls == SRC_LANE) idx |= (uint32_t)((lane >> v) & 1) << q;
+                    else if (cls == SRC_WAVE) idx |= (uint32_t)((wave >> v) & 1) << q;
+                    else if (cls == SRC_GLOB) idx |= (uint32_t)((base >> v) & 1ull) << q;
                 }
-                // table bits held in registers: at most two take the fast path
-                // (the four candidate phases are loaded once per thread and
-                // selected per slot with uniform conditions)
-                int nq = 0, qa = -1, qb = -1;
-#pragma unroll
-                for (int q = 0; q < 6; ++q)
-                    if (rm[q]) {
-                        if (nq == 0) qa = q;
-                        else if (nq == 1) qb = q;
-                        ++nq;
-                    }
-                if (nq <= 2) {
-                    const uint32_t ba = qa >= 0 ? 1u << qa : 0u, bb = qb >= 0 ? 1u << qb : 0u;
-                    const uint32_t ma = qa >= 0 ? rm[qa] : 0u, mb = qb >= 0 ? rm[qb] : 0u;
-                    V pv[4];
-                    pv[0] = ldc(tab, (int)ithr);
-                    pv[1] = ldc(tab, (int)(ithr ^ ba));
-                    pv[2] = ldc(tab, (int)(ithr ^ bb));
-                    pv[3] = ldc(tab, (int)(ithr ^ (ba | bb)));
-                    sfor<NR>([&](auto jc) {
-                        constexpr int j = decltype(jc)::value;
-                        const int r = (((uint32_t)j & ma) ? 1 : 0) | (((uint32_t)j & mb) ? 2 : 0);   // uniform
-                        if (r == 0) cmul_to(a[j], pv[0]);
-                        else if (r == 1) cmul_to(a[j], pv[1]);
-                        else if (r == 2) cmul_to(a[j], pv[2]);
-                        else cmul_to(a[j], pv[3]);
-                    });
+                return idx;
+            };
+            auto full = [&](V (&m)[4]) {
+                if constexpr (sizeof(T) == 4) {
+                    for (int e = 0; e < 4; ++e) m[e] = V{op.k[2 * e], op.k[2 * e + 1]};
                 } else {
-                    sfor<NR>([&](auto jc) {
-                        constexpr int j = decltype(jc)::value;
-                        uint32_t idx = ithr;
-#pragma unroll
-                        for (int q = 0; q < 6; ++q)
-                            if ((uint32_t)j & rm[q]) idx ^= 1u << q;
-                        cmul_to(a[j], ldc(tab, (int)idx));
-                    });
+                    const double* __restrict__ more = prog[i].more;
+                    m[0] = V{op.k[0], op.k[1]};
+                    m[1] = V{op.k[2], op.k[3]};
+                    m[2] = V{more[0], more[1]};
+                    m[3] = V{more[2], more[3]};
                 }
+            };
+#define QOPS_CASE_IF(CODE, COND, BODY)                                                                       \
+    case CODE:                                                                                               \
+        if constexpr (COND) {                                                                                \
+            BODY;                                                                                            \
+        } else                                                                                               \
+            __builtin_unreachable();                                                                         \
+        break;
+#define QOPS_1Q_CASES(B, C)                                                                                  \
+    QOPS_CASE_IF(RC_X_REG + 3 * B + C, (B < R), (xgate_reg_b<B, R, C>(a, creg, cval, C ? tok_of() : true)))  \
+    QOPS_CASE_IF(RC_1Q_REG + 3 * B + C, (B < R), V m[4]; full(m);                                            \
+                 (oneq_reg_b<B, R, C>(a, m[0], m[1], m[2], m[3], creg, cval, C ? tok_of() : true)))
+#define QOPS_SHEAR_CASE(B, F, TY)                                                                            \
+    QOPS_CASE_IF(RC_SHEAR_REG + 6 * B + 3 * F + TY, (B < R),                                                 \
+                 (shear_reg_b<B, R, F, TY>(a, op.k[0], op.k[1], op.k[2], op.k[3])))
+#define QOPS_BIT_CASES(B)                                                                                    \
+    QOPS_1Q_CASES(B, 0) QOPS_1Q_CASES(B, 1) QOPS_1Q_CASES(B, 2)                                              \
+    QOPS_SHEAR_CASE(B, 0, 0) QOPS_SHEAR_CASE(B, 0, 1) QOPS_SHEAR_CASE(B, 0, 2)                               \
+    QOPS_SHEAR_CASE(B, 1, 0) QOPS_SHEAR_CASE(B, 1, 1) QOPS_SHEAR_CASE(B, 1, 2)                               \
+    QOPS_COND_CASES((B < R), RC_SIGN1 + 2 * B, RC_PHASE1 + 2 * B, 1u << B, 0u)                               \
+    QOPS_COND_CASES((B < R), RC_SIGN1 + 2 * B + 1, RC_PHASE1 + 2 * B + 1, 1u << B, 1u << B)                  \
+    QOPS_CASE_IF(RC_DIAG1 + B, (B < R), (diag_regs<T, R, 1u << B, 0u>(a, tab_of(), ithr_of(), op.aux)))
+#define QOPS_COND_CASES(COND, SIGN, PHASE, M, VAL)                                                           \
+    QOPS_CASE_IF(SIGN, COND, (sign_slots<R, M, VAL>(a, sign_of())))                                          \
+    QOPS_CASE_IF(PHASE, COND, (phase_slots<R, M, VAL>(a, phase_of())))
+#define QOPS_PAIR_CASES(B, C)                                                                                \
+    QOPS_PAIR_VALUE(B, C, 0) QOPS_PAIR_VALUE(B, C, 1) QOPS_PAIR_VALUE(B, C, 2) QOPS_PAIR_VALUE(B, C, 3)      \
+    QOPS_CASE_IF(RC_DIAG2 + C * (C - 1) / 2 + B, (C < R),                                                    \
+                 (diag_regs<T, R, 1u << B, 1u << C>(a, tab_of(), ithr_of(), op.aux)))                        \
+    QOPS_CX_CASE(B, C, 0) QOPS_CX_CASE(B, C, 1)
+#define QOPS_PAIR_VALUE(B, C, P)                                                                             \
+    QOPS_COND_CASES((C < R), RC_SIGN2 + 4 * (C * (C - 1) / 2 + B) + P,                                       \
+                    RC_PHASE2 + 4 * (C * (C - 1) / 2 + B) + P, (1u << B | 1u << C),                          \
+                    ((P & 1 ? 1u << B : 0u) | (P & 2 ? 1u << C : 0u)))
+#define QOPS_CX_CASE(B, C, P)                                                                                \
+    QOPS_CASE_IF(RC_CX_REG + 2 * (2 * (C * (C - 1) / 2 + B)) + P, (C < R),                                   \
+                 (cx_slots<B, R, 1u << C, P ? 1u << C : 0u>(a)))                                             \
+    QOPS_CASE_IF(RC_CX_REG + 2 * (2 * (C * (C - 1) / 2 + B) + 1) + P, (C < R),                               \
+                 (cx_slots<C, R, 1u << B, P ? 1u << B : 0u>(a)))
+#define QOPS_LANE_CASE(B, EX, TY)                                                                            \
+    QOPS_CASE_IF(RC_SHEAR_LANE + 6 * B + 3 * EX + TY, true,                                                  \
+                 (shear_lane_b<B, R, EX != 0, TY>(lane, a, op.k[0], op.k[1], op.k[2], op.k[3])))
+#define QOPS_LANE_CASES(B)                                                                                   \
+    QOPS_LANE_CASE(B, 0, 0) QOPS_LANE_CASE(B, 0, 1) QOPS_LANE_CASE(B, 0, 2)                                  \
+    QOPS_LANE_CASE(B, 1, 0) QOPS_LANE_CASE(B, 1, 1) QOPS_LANE_CASE(B, 1, 2)
+#define QOPS_LANE_1Q(C)                                                                                      \
+    QOPS_CASE_IF(RC_X_LANE + C, true, (xgate_lane<R, C>(op.aux, lane, a, creg, cval, C ? tok_of() : true)))  \
+    QOPS_CASE_IF(RC_1Q_LANE + C, true, V m[4]; full(m);                                                      \
+                 (oneq_lane<R, C>(op.aux, lane, a, m[0], m[1], m[2], m[3], creg, cval, C ? tok_of() : true)))
+            switch (op.code) {
+            QOPS_BIT_CASES(0) QOPS_BIT_CASES(1) QOPS_BIT_CASES(2) QOPS_BIT_CASES(3) QOPS_BIT_CASES(4)
+            QOPS_PAIR_CASES(0, 1) QOPS_PAIR_CASES(0, 2) QOPS_PAIR_CASES(1, 2) QOPS_PAIR_CASES(0, 3)
+            QOPS_PAIR_CASES(1, 3) QOPS_PAIR_CASES(2, 3) QOPS_PAIR_CASES(0, 4) QOPS_PAIR_CASES(1, 4)
+            QOPS_PAIR_CASES(2, 4) QOPS_PAIR_CASES(3, 4)
+            QOPS_LANE_CASES(0) QOPS_LANE_CASES(1) QOPS_LANE_CASES(2)
+            QOPS_LANE_CASES(3) QOPS_LANE_CASES(4) QOPS_LANE_CASES(5)
+            QOPS_LANE_1Q(0) QOPS_LANE_1Q(1) QOPS_LANE_1Q(2)
+            QOPS_COND_CASES(true, RC_SIGN0, RC_PHASE0, 0u, 0u)
+            QOPS_CASE_IF(RC_DIAG0, true, (phase_slots<R, 0u, 0u>(a, ldc(tab_of(), (int)ithr_of()))))
+            case RC_SIGN: {
+                const T sgn = sign_of();
+                sfor<NR>([&](auto jc) {
+                    constexpr int j = decltype(jc)::value;
+                    if (((uint32_t)j & creg) == cval) {
+                        a[j].x *= sgn;
+                        a[j].y *= sgn;
+                    }
+                });
                 pin_tile(a);
                 break;
             }
-            case OP_REMAP: {
-                flip_map<R, W>(ms, op.c_reg);
+            case RC_PHASE: {
+                const V ph = phase_of();
+                sfor<NR>([&](auto jc) {
+                    constexpr int j = decltype(jc)::value;
+                    if (((uint32_t)j & creg) == cval) cmul_to(a[j], ph);
+                });
+                pin_tile(a);
+                break;
+            }
+            case RC_DIAG: {
+                const T* tab = tab_of();
+                const uint32_t ithr = ithr_of();
+                uint32_t rm[6];
+#pragma unroll
+                for (int q = 0; q < 6; ++q) rm[q] = q < (op.aux & 255) && op.pos[q] >> 8 == SRC_REG ? 1u << (op.pos[q] & 255) : 0u;
+                sfor<NR>([&](auto jc) {
+                    constexpr int j = decltype(jc)::value;
+                    uint32_t idx = ithr;
+#pragma unroll
+                    for (int q = 0; q < 6; ++q)
+                        if ((uint32_t)j & rm[q]) idx ^= 1u << q;
+                    cmul_to(a[j], ldc(tab, (int)idx));
+                });
+                pin_tile(a);
+                break;
+            }
+            case RC_REMAP: {
+                flip_map<R, W>(ms, creg);
                 __syncthreads();
                 sfor<NR>([&](auto jc) { lds[ms.tlds + reg_lds(ms, decltype(jc)::value)] = a[decltype(jc)::value]; });
                 __syncthreads();
-                set_map<R, W>(ms, (uint32_t)op.b, up_phys, lane, wave);
+                set_map<R, W>(ms, (uint32_t)op.aux, up_phys, lane, wave);
                 sfor<NR>([&](auto jc) { a[decltype(jc)::value] = lds[ms.tlds + reg_lds(ms, decltype(jc)::value)]; });
                 pin_tile(a);
                 break;
@@ -608,71 +638,66 @@ __device__ __forceinline__ void reg_tile(typename CxT<T>::V* __restrict__ st, co
     }
 }
 
+// Tile numbers (single circuit) or (circuit, tile) items (batched executor:
+// pass `pass` of every circuit in `items`, all planned with this split), in a
+// grid-stride loop.  One kernel for both, as the body is most of the code.
 template <typename T, int R, int W>
 __global__ void __launch_bounds__(64 << W)
-tile_pass_kernel(typename CxT<T>::V* __restrict__ st, const PassHdr* __restrict__ hp, const DevOp* __restrict__ ops,
-                 const T* __restrict__ coef, uint64_t ntiles)
+tile_pass_kernel(typename CxT<T>::V* __restrict__ state, const PassHdr* __restrict__ hdrs, const DevOp* __restrict__ ops,
+                 const T* __restrict__ coef, uint64_t count, const BatchItem* __restrict__ items,
+                 const BatchCirc* __restrict__ circs, int pass)
 {
     using V = typename CxT<T>::V;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     V* lds = reinterpret_cast<V*>(smem_raw);
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x)
-        reg_tile<T, R, W>(st, hp, ops, coef, tile, lds, lane, wave, false);
+    for (uint64_t i = blockIdx.x; i < count; i += gridDim.x) {
+        V* st = state;
+        int hdr = 0;            // the pass (single circuit) or its place among the batch's headers
+        uint64_t tile = i;
+        if (items) {
+            const BatchItem it = items[i];
+            st = reinterpret_cast<V*>(circs[it.c].state);
+            hdr = circs[it.c].hdr0 + pass;
+            tile = (uint64_t)it.tile;
+        }
+        reg_tile<T, R, W>(st, hdrs + hdr, ops, coef, tile, lds, lane, wave, items && pass == 0);
+    }
 }
 
-// Batched executor: register-tile pass `pass` of every circuit in `items`
-// (all planned with the same register/wave split).
 template <typename T, int R, int W>
-__global__ void __launch_bounds__(64 << W)
-batch_reg_kernel(const BatchItem* __restrict__ items, int nitems, const BatchCirc* __restrict__ circs,
-                 const PassHdr* __restrict__ hdrs, const DevOp* __restrict__ ops, const T* __restrict__ coef, int pass)
+static hipError_t launch_reg(void* state, const PassHdr* hdrs, const DevOp* ops, const void* coef, uint64_t count,
+                             const BatchItem* items, const BatchCirc* circs, int pass, uint64_t grid, int lds_bytes,
+                             hipStream_t s)
 {
-    using V = typename CxT<T>::V;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    V* lds = reinterpret_cast<V*>(smem_raw);
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    for (int i = blockIdx.x; i < nitems; i += gridDim.x) {
-        const BatchItem it = items[i];
-        const BatchCirc c = circs[it.c];
-        reg_tile<T, R, W>(reinterpret_cast<V*>(c.state), hdrs + c.hdr0 + pass, ops, coef, (uint64_t)it.tile, lds,
-                          lane, wave, pass == 0);
-    }
+    auto fn = tile_pass_kernel<T, R, W>;
+    // dynamic LDS beyond 64 KiB has to be allowed (per device)
+    if (lds_bytes > 64 * 1024)
+        if (hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes))
+            return e;
+    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(64 << W), lds_bytes, s,
+                       reinterpret_cast<typename CxT<T>::V*>(state), hdrs, ops, reinterpret_cast<const T*>(coef), count,
+                       items, circs, pass);
+    return hipGetLastError();
 }
 
 template <typename T, int R, int W>
 hipError_t launch_tile_t(void* state, const PassHdr* hdr, const DevOp* ops, const void* coef, uint64_t ntiles,
-                                int lds_bytes, int grid_cap, hipStream_t s)
+                         int lds_bytes, int grid_cap, hipStream_t s)
 {
-    using V = typename CxT<T>::V;
-    auto fn = tile_pass_kernel<T, R, W>;
-    static bool attr_done = false;
-    if (!attr_done) {
-        (void)hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, tile_max_lds_bytes());
-        attr_done = true;
-    }
     uint64_t grid = ntiles;
     if (grid_cap > 0 && grid > (uint64_t)grid_cap) grid = (uint64_t)grid_cap;
     if (grid > 0x7fffffffull) grid = 0x7fffffffull;
-    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(64 << W), lds_bytes, s, reinterpret_cast<V*>(state), hdr, ops,
-                       reinterpret_cast<const T*>(coef), ntiles);
-    return hipGetLastError();
+    return launch_reg<T, R, W>(state, hdr, ops, coef, ntiles, nullptr, nullptr, 0, grid, lds_bytes, s);
 }
 
 template <typename T, int R, int W>
 hipError_t launch_batch_reg_t(const BatchItem* items, int nitems, const BatchCirc* circs, const PassHdr* hdrs,
-                                     const DevOp* ops, const void* coef, int pass, int lds_bytes, int grid,
-                                     hipStream_t s)
+                              const DevOp* ops, const void* coef, int pass, int lds_bytes, int grid, hipStream_t s)
 {
-    if (hipError_t e = hipFuncSetAttribute((const void*)batch_reg_kernel<T, R, W>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes))
-        return e;
-    const int g = std::max(1, std::min(nitems, grid));
-    hipLaunchKernelGGL((batch_reg_kernel<T, R, W>), dim3(g), dim3(64 << W), lds_bytes, s, items, nitems, circs, hdrs,
-                       ops, reinterpret_cast<const T*>(coef), pass);
-    return hipGetLastError();
+    return launch_reg<T, R, W>(nullptr, hdrs, ops, coef, (uint64_t)nitems, items, circs, pass,
+                               (uint64_t)std::max(1, std::min(nitems, grid)), lds_bytes, s);
 }
 
 template hipError_t launch_tile_t<QOPS_RT_T, QOPS_RT_R, QOPS_RT_W>(void*, const PassHdr*, const DevOp*, const void*,

@@ -10,8 +10,7 @@ namespace qops {
 
 // (R, W): register and wave bits; the build script compiles each for both
 // precisions.
-#define QOPS_TILE_VARIANTS(X) \
-    X(4, 0) X(4, 1) X(4, 2) X(5, 0) X(5, 1) X(5, 2)
+#define QOPS_TILE_VARIANTS(X) X(3, 2) X(3, 3) X(4, 0) X(4, 2) X(4, 3)
 
 template <typename T, int R, int W>
 hipError_t launch_tile_t(void* state, const PassHdr* hdr, const DevOp* ops, const void* coef, uint64_t ntiles,

@@ -149,26 +149,13 @@ int32_t ensure_scratch(qops_sim* h, size_t doubles)
 PlanParams params_from(const qops_plan_opts* o, int n, int prec)
 {
     PlanParams par;
-    // register tile passes: complex64 defaults to 4 register bits and no
-    // wave bits (10-bit tiles, light enough for six waves per SIMD), which
-    // measured 28-30 % faster than 13-bit tiles (5 register + 2 wave bits)
-    // on gate-level circuits; LDS tile passes keep the largest tile
-    par.R = 4;
-    par.W = prec == QOPS_C64 ? 0 : 2;
     par.L_lds = prec == QOPS_C64 ? 13 : 12;
     par.state_lds_max_n = 12;
     if (!o) return par;
     par.mode = o->mode;
     par.swap_mode = o->swap_mode;
     if (o->tile_upper > 0) {
-        // an explicit width: up to 5 (complex64) / 4 (complex128) register
-        // bits, the rest wave bits
-        par.R = prec == QOPS_C64 ? 5 : 4;
-        par.W = std::max(0, o->tile_upper - par.R);
-        if (o->tile_upper < par.R) {
-            par.R = std::max(4, o->tile_upper);
-            par.W = 0;
-        }
+        par.reg_up = o->tile_upper;
         par.L_lds = std::min(6 + o->tile_upper, prec == QOPS_C64 ? 13 : 12);
     }
     par.max_fuse_k = o->max_fuse_k > 0 ? o->max_fuse_k : 1;
@@ -363,7 +350,7 @@ int32_t qops_plan_stats_get(const qops_plan* p, qops_plan_stats* s)
     s->n_ops = (int32_t)q.lops.size();
     s->n_gates_in = (int32_t)q.gates.size();
     s->n_virtual_swaps = q.n_virtual_swaps;
-    s->tile_upper = q.par.R + q.par.W;
+    s->tile_upper = q.par.reg_up > 0 ? std::max(4, q.par.reg_up) : q.reg_upper;
     s->max_fuse_k = q.par.max_fuse_k;
     s->n_folded = q.n_folded;
     s->predicted_s = q.predicted_s;

@@ -81,3 +81,35 @@ def test_chain_ends_in_a_singular_matrix(q, prec, tol):
     got = sim.state().astype(np.complex128)
     sim.close()
     assert np.max(np.abs(got - orc.run_circuit(c))) <= tol
+
+
+@pytest.mark.parametrize("prec,tol", [(0, 2e-5), (1, 1e-12)])
+@pytest.mark.parametrize("n,tile_upper", [(10, 0), (11, 0), (12, 0), (13, 0), (13, 4), (13, 5), (13, 6), (13, 7)])
+def test_every_register_condition(q, prec, tol, n, tile_upper):
+    """CZ, CP, CX and RZZ on every pair of qubits, triple phases and a
+    four-bit diagonal between layers of 2x2s (so that register bits are met
+    with slots in order and exchanged): the bodies compiled per register bit,
+    pair and required value, the general ones, and 10..12-qubit states that
+    are one register tile."""
+    rng = np.random.default_rng(n + 100 * tile_upper)
+    g = []
+    pairs = [(int(a), int(b)) for a in range(n) for b in range(n) if a != b]
+    rng.shuffle(pairs)
+    for i, (a, b) in enumerate(pairs):
+        if i % 12 == 0:
+            g += [W.Gate("u3", (b2,), (), tuple(map(float, rng.uniform(0, 6.28, 3)))) for b2 in range(n)]
+        g.append(W.Gate(("cz", "cx", "cp", "rzz")[i % 4], (a, b), (), (float(rng.uniform(0, 6.28)),) if i % 4 > 1 else ()))
+        if i % 9 == 4:
+            c = int(rng.choice([v for v in range(n) if v not in (a, b)]))
+            g.append(W.Gate("z" if i % 2 else "p", (a,), (b, c), () if i % 2 else (0.8,)))
+            g.append(W.Gate("x", (c,), (a, b)))
+        if i % 17 == 3:
+            c, d = (int(v) for v in rng.choice([v for v in range(n) if v not in (a, b)], 2, replace=False))
+            g += [W.Gate("rzz", (a, c), (), (0.3,)), W.Gate("rzz", (c, d), (), (0.5,)), W.Gate("rzz", (d, b), (), (0.7,))]
+    circ = W.Circuit(n, g, x0=5)
+    sim = q.Simulator(n, prec)
+    sim.init_basis(5)
+    sim.run(q.Plan(n, g, precision=prec, tile_upper=tile_upper))
+    got = sim.state().astype(np.complex128)
+    sim.close()
+    assert np.max(np.abs(got - orc.run_circuit(circ))) <= tol
