@@ -115,24 +115,24 @@ Err validate_gates(int n, const qops_gate* g, size_t ng, bool check_unitary)
     if (ng > 0 && !g) return mkerr(QOPS_INVALID_ARG, "null gate list");
     for (size_t i = 0; i < ng; ++i) {
         const qops_gate& x = g[i];
-        const std::string at = " (gate " + std::to_string(i) + ")";
-        if (x.kind >= QOPS_NUM_KINDS) return mkerr(QOPS_INVALID_ARG, "unknown gate kind" + at);
+        auto at = [i]() { return " (gate " + std::to_string(i) + ")"; };
+        if (x.kind >= QOPS_NUM_KINDS) return mkerr(QOPS_INVALID_ARG, "unknown gate kind" + at());
         const int ar = gate_arity(x.kind);
         const int k = x.kind == QOPS_DENSE ? x.k : ar;
         if (x.kind == QOPS_DENSE) {
-            if (x.k < 1 || x.k > QOPS_MAX_K) return mkerr(QOPS_UNSUPPORTED, "DENSE k must be 1..6" + at);
-            if (!x.mat) return mkerr(QOPS_INVALID_ARG, "DENSE gate without a matrix" + at);
+            if (x.k < 1 || x.k > QOPS_MAX_K) return mkerr(QOPS_UNSUPPORTED, "DENSE k must be 1..6" + at());
+            if (!x.mat) return mkerr(QOPS_INVALID_ARG, "DENSE gate without a matrix" + at());
         } else if (x.k != ar) {
-            return mkerr(QOPS_INVALID_ARG, "k does not match the gate kind" + at);
+            return mkerr(QOPS_INVALID_ARG, "k does not match the gate kind" + at());
         }
-        if (x.n_ctrl > QOPS_MAX_CTRL) return mkerr(QOPS_UNSUPPORTED, "more than 4 controls" + at);
+        if (x.n_ctrl > QOPS_MAX_CTRL) return mkerr(QOPS_UNSUPPORTED, "more than 4 controls" + at());
         if (diag_kind(x.kind) && k + x.n_ctrl > 6)
-            return mkerr(QOPS_UNSUPPORTED, "diagonal gate with more than 6 qubits" + at);
+            return mkerr(QOPS_UNSUPPORTED, "diagonal gate with more than 6 qubits" + at());
         uint64_t seen = 0;
         for (int j = 0; j < k + x.n_ctrl; ++j) {
             const int q = j < k ? x.q[j] : x.ctrl[j - k];
-            if (q < 0 || q >= n) return mkerr(QOPS_QUBIT_RANGE, "qubit out of range" + at);
-            if (seen & (1ull << q)) return mkerr(QOPS_DUPLICATE_QUBIT, "qubit listed twice" + at);
+            if (q < 0 || q >= n) return mkerr(QOPS_QUBIT_RANGE, "qubit out of range" + at());
+            if (seen & (1ull << q)) return mkerr(QOPS_DUPLICATE_QUBIT, "qubit listed twice" + at());
             seen |= 1ull << q;
         }
         if (check_unitary && x.kind == QOPS_DENSE) {
@@ -147,7 +147,7 @@ Err validate_gates(int n, const qops_gate* g, size_t ng, bool check_unitary)
                     for (int s = 0; s < d; ++s) acc += std::conj(m[(size_t)s * d + r]) * m[(size_t)s * d + c2];
                     worst = std::max(worst, std::abs(acc - (r == c2 ? cd(1) : cd(0))));
                 }
-            if (worst > 1e-9) return mkerr(QOPS_NOT_UNITARY, "DENSE matrix is not unitary" + at);
+            if (worst > 1e-9) return mkerr(QOPS_NOT_UNITARY, "DENSE matrix is not unitary" + at());
         }
     }
     return Err{};
@@ -162,6 +162,7 @@ static Err lower(int n, const qops_gate* g, size_t ng, int swap_mode, std::vecto
 {
     (void)n;
     std::vector<cd> u;
+    out.reserve(out.size() + ng);
     for (size_t i = 0; i < ng; ++i) {
         const qops_gate& x = g[i];
         const int k = x.kind == QOPS_DENSE ? x.k : gate_arity(x.kind);
@@ -223,7 +224,7 @@ static Err lower(int n, const qops_gate* g, size_t ng, int swap_mode, std::vecto
             o.cmask = cm;
             o.m = u;
         }
-        out.push_back(o);
+        out.push_back(std::move(o));
     }
     return Err{};
 }
@@ -232,12 +233,12 @@ static Err lower(int n, const qops_gate* g, size_t ng, int swap_mode, std::vecto
 // Merging (single-qubit merging and diagonal fusion), exact in FP64
 // ---------------------------------------------------------------------------
 
-static void mat2_mul(const std::vector<cd>& a, const std::vector<cd>& b, std::vector<cd>& out)
+static Mat mat2_mul(const Mat& a, const Mat& b)
 {
-    out = {a[0] * b[0] + a[1] * b[2], a[0] * b[1] + a[1] * b[3], a[2] * b[0] + a[3] * b[2], a[2] * b[1] + a[3] * b[3]};
+    return {a[0] * b[0] + a[1] * b[2], a[0] * b[1] + a[1] * b[3], a[2] * b[0] + a[3] * b[2], a[2] * b[1] + a[3] * b[3]};
 }
 
-static bool is_identity2(const std::vector<cd>& m)
+static bool is_identity2(const Mat& m)
 {
     return std::abs(m[0] - 1.0) < 1e-14 && std::abs(m[1]) < 1e-14 && std::abs(m[2]) < 1e-14 &&
            std::abs(m[3] - 1.0) < 1e-14;
@@ -259,7 +260,8 @@ static bool merge_diag(LOp& y, const LOp& x)
             bits[nb++] = x.t[j];
             ub |= 1ull << x.t[j];
         }
-    std::vector<cd> tab((size_t)1 << nb);
+    Mat tab;
+    tab.assign((size_t)1 << nb, cd(0));
     for (size_t idx = 0; idx < tab.size(); ++idx) {
         size_t iy = 0, ix = 0;
         for (int j = 0; j < y.k; ++j) iy |= ((idx >> j) & 1) << j;
@@ -281,7 +283,7 @@ static bool merge_diag(LOp& y, const LOp& x)
 
 // Left-multiplies the block matrix M (2^|Q| square, row-major, index bit i
 // <-> physical bit Q[i]) by operation o embedded on the block's bits.
-static void block_apply(std::vector<cd>& M, const std::vector<int>& Q, const LOp& o)
+static void block_apply(Mat& M, const std::vector<int>& Q, const LOp& o)
 {
     const int nb = (int)Q.size();
     const uint32_t D = 1u << nb;
@@ -353,6 +355,7 @@ static void merge_dense_priced(std::vector<LOp>& ops, const double* cost)
     const size_t n = ops.size();
     const size_t window = 64;
     auto mergeable = [](const LOp& o) { return o.kind == LOp::DENSE && o.cmask == 0 && o.k >= 2 && !o.dead; };
+    if (std::count_if(ops.begin(), ops.end(), mergeable) < 2) return;
     std::vector<char> placed(n, 0);
     std::vector<LOp> out;
     out.reserve(n);
@@ -361,7 +364,7 @@ static void merge_dense_priced(std::vector<LOp>& ops, const double* cost)
         placed[first] = 1;
         const LOp& a = ops[first];
         if (!mergeable(a)) {
-            out.push_back(a);
+            out.push_back(std::move(ops[first]));
             continue;
         }
         uint64_t Qm = a.touch();
@@ -500,9 +503,7 @@ static void merge_ops(std::vector<LOp>& in, std::vector<LOp>& out)
                 LOp& y = out[j];
                 if (y.dead) continue;
                 if (y.kind == LOp::ONEQ && y.t[0] == x.t[0] && y.cmask == x.cmask) {
-                    std::vector<cd> p;
-                    mat2_mul(x.m, y.m, p);
-                    y.m.swap(p);
+                    y.m = mat2_mul(x.m, y.m);
                     y.nmerged += x.nmerged;
                     if (is_identity2(y.m)) y.dead = true;
                     merged = true;
@@ -510,7 +511,7 @@ static void merge_ops(std::vector<LOp>& in, std::vector<LOp>& out)
                 }
                 if (x.cmask == 0 && y.kind == LOp::DIAG && y.k == 1 && y.t[0] == x.t[0]) {
                     // U * diag(d): the diagonal joins the 2x2
-                    std::vector<cd> p = {x.m[0] * y.m[0], x.m[1] * y.m[1], x.m[2] * y.m[0], x.m[3] * y.m[1]};
+                    Mat p = {x.m[0] * y.m[0], x.m[1] * y.m[1], x.m[2] * y.m[0], x.m[3] * y.m[1]};
                     y.kind = LOp::ONEQ;
                     y.k = 1;
                     y.cmask = 0;
@@ -540,14 +541,13 @@ static void merge_ops(std::vector<LOp>& in, std::vector<LOp>& out)
                 for (int b = 0; same_bits && b < x.k; ++b) same_bits = y.t[b] == x.t[b];
                 const bool compatible = (!x.cphase && !y.cphase) || (x.cphase && y.cphase && same_bits);
                 if (y.kind == LOp::DIAG && diag_cand < 0 && compatible) {
-                    LOp probe = y;
-                    if (merge_diag(probe, x)) {
+                    if (__builtin_popcountll(y.touch() | xb) <= 6) {   // the merged table fits
                         diag_cand = j;
                         if (x.k != 1) break;
                     }
                 }
                 if (x.k == 1 && y.kind == LOp::ONEQ && y.cmask == 0 && y.t[0] == x.t[0]) {
-                    std::vector<cd> p = {x.m[0] * y.m[0], x.m[0] * y.m[1], x.m[1] * y.m[2], x.m[1] * y.m[3]};
+                    Mat p = {x.m[0] * y.m[0], x.m[0] * y.m[1], x.m[1] * y.m[2], x.m[1] * y.m[3]};
                     y.m.swap(p);
                     y.nmerged += x.nmerged;
                     merged = true;
@@ -557,7 +557,7 @@ static void merge_ops(std::vector<LOp>& in, std::vector<LOp>& out)
             }
             if (!merged && diag_cand >= 0) merged = merge_diag(out[diag_cand], x);
         }
-        if (!merged) out.push_back(x);
+        if (!merged) out.push_back(std::move(x));
     }
     std::vector<LOp> alive;
     alive.reserve(out.size());
@@ -570,7 +570,8 @@ static void merge_ops(std::vector<LOp>& in, std::vector<LOp>& out)
 // Device program emission
 // ---------------------------------------------------------------------------
 
-static int push_coef(Plan& p, const std::vector<cd>& m)
+template <typename M>
+static int push_coef(Plan& p, const M& m)
 {
     const int off = (int)p.coef.size();
     for (const cd& v : m) {
@@ -864,7 +865,7 @@ static void emit_lds_op(Plan& p, const LOp& o, int L, F tpos, PassPlan& pp, bool
         d.coef = push_coef(p, o.m);
         pp.n_diag_ops++;
     } else {
-        std::vector<cd> m = o.m;
+        std::vector<cd> m(o.m.begin(), o.m.end());
         int k = o.k;
         int t[6];
         for (int j = 0; j < k; ++j) t[j] = o.t[j];
@@ -953,7 +954,7 @@ struct Chain {
     }
 };
 
-static bool unitary2(const std::vector<cd>& m)
+static bool unitary2(const Mat& m)
 {
     const double n0 = std::norm(m[0]) + std::norm(m[2]), n1 = std::norm(m[1]) + std::norm(m[3]);
     return std::abs(n0 - 1.0) < 1e-9 && std::abs(n1 - 1.0) < 1e-9 &&
@@ -1049,7 +1050,7 @@ static void shear_lane_form(const Cl (&N)[4], int& ex, Cl& w, Cl& v, Cl& d0, Cl&
     v = (ex ? N[3] : N[2]) / d1;
 }
 
-static bool exact_x(const std::vector<cd>& m)
+static bool exact_x(const Mat& m)
 {
     return m[0] == cd(0) && m[1] == cd(1) && m[2] == cd(1) && m[3] == cd(0);
 }
@@ -1063,8 +1064,14 @@ struct RegRec {
     uint64_t c_glob = 0;
     int coef = 0, aux = 0, npos = 0;
     int pos[6] = {0};
-    std::vector<cd> k;
+    int nk = 0;
+    cd k[4];
 
+    void set(std::initializer_list<cd> v)
+    {
+        nk = 0;
+        for (const cd& x : v) k[nk++] = x;
+    }
     template <typename T>
     void fill(RegOpT<T>& r) const
     {
@@ -1075,8 +1082,8 @@ struct RegRec {
         r.aux = aux;
         r.c_glob = c_glob;
         for (int j = 0; j < npos; ++j) r.pos[j] = pos[j];
-        for (size_t e = 0; e < k.size(); ++e) {
-            T* dst = at(r, (int)e);
+        for (int e = 0; e < nk; ++e) {
+            T* dst = at(r, e);
             dst[0] = (T)k[e].real();
             dst[1] = (T)k[e].imag();
         }
@@ -1181,8 +1188,8 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
         }
         RegRec d;
         auto enc_ctrl = [&](uint64_t cm) {
-            for (int b = 0; b < 64; ++b) {
-                if (!(cm & (1ull << b))) continue;
+            for (; cm; cm &= cm - 1) {
+                const int b = __builtin_ctzll(cm);
                 if (b < 6) {
                     d.c_lane |= 1u << b;
                     continue;
@@ -1234,11 +1241,11 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
                     flip |= (uint32_t)fl << rb;
                     d.code = RC_SHEAR_REG + 6 * rb + 3 * form + coef_type(w, v);
                 }
-                d.k = {w.to_cd(), v.to_cd()};
+                d.set({w.to_cd(), v.to_cd()});
             } else {
                 d.code = lane ? RC_1Q_LANE : RC_1Q_REG + 3 * rb;
                 d.aux = b;
-                d.k = {N[0].to_cd(), N[1].to_cd(), N[2].to_cd(), N[3].to_cd()};
+                d.set({N[0].to_cd(), N[1].to_cd(), N[2].to_cd(), N[3].to_cd()});
             }
         } else if (o.kind == LOp::ONEQ) {
             const bool lane = o.t[0] < 6, is_x = exact_x(o.m);
@@ -1255,8 +1262,8 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
                 d.code = (lane ? (int)RC_X_LANE : RC_X_REG + 3 * rb) + c;
             } else {
                 d.code = (lane ? (int)RC_1Q_LANE : RC_1Q_REG + 3 * rb) + c;
-                d.k.assign(o.m.begin(), o.m.end());
-                if (!lane && (flip >> rb & 1u)) d.k = {o.m[3], o.m[2], o.m[1], o.m[0]};   // on exchanged slots
+                if (!lane && (flip >> rb & 1u)) d.set({o.m[3], o.m[2], o.m[1], o.m[0]});   // on exchanged slots
+                else d.set({o.m[0], o.m[1], o.m[2], o.m[3]});
                 pp.flops += 16.0 * std::ldexp(1.0, p.n - __builtin_popcountll(o.cmask));
             }
         } else if (o.cphase) {
@@ -1278,7 +1285,7 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
             } else {
                 d.code = sign ? RC_SIGN : RC_PHASE;
             }
-            d.k = {ph};
+            d.set({ph});
             pp.n_diag_ops++;
             pp.flops += 6.0 * std::ldexp(1.0, p.n - o.k);
         } else {   // DIAG
@@ -1676,7 +1683,7 @@ static void pack(Plan& p)
     auto flush = [&]() {
         if (!cur.lop.empty()) {
             finish_pass(p, cur, dense ? S4 : S, dense);
-            p.passes.push_back(cur);
+            p.passes.push_back(std::move(cur));
         }
         cur = PassPlan();
         cur.R = R;
@@ -1695,7 +1702,8 @@ static void pack(Plan& p)
     // any bit of the other (shared bits are then controls or diagonal bits of
     // both).  A physical swap ends the scan.
     const size_t nl = p.lops.size();
-    const size_t window = 256;
+    // (a tile that holds every bit takes every operation)
+    const size_t window = cap_reg >= n - 6 ? nl : 256;
     std::vector<char> placed(nl, 0);
     // non-diagonal target bits outside the fixed bits of a register tile (6)
     // or of an LDS tile (4)
@@ -1995,6 +2003,7 @@ Err update_plan(Plan& p, const qops_gate* g, size_t ng)
     std::swap(q.d_hdr, p.d_hdr);
     std::swap(q.d_ops, p.d_ops);
     std::swap(q.d_coef, p.d_coef);
+    std::swap(q.d_bytes, p.d_bytes);
     q.predicted_s = p.predicted_s;
     p = std::move(q);
     p.dirty = true;

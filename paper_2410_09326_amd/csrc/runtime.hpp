@@ -20,6 +20,14 @@ struct qops_sim {
     double* scratch = nullptr;        // reductions / readout staging
     size_t scratch_doubles = 0;
     qops::Plan* last_plan = nullptr;  // kept alive until the next apply / destroy
+    // qops_apply's program: one device block that every call rewrites in
+    // stream order, filled from pinned memory (free again once `stage_done`)
+    void* image = nullptr;
+    size_t image_bytes = 0;
+    void* stage = nullptr;
+    size_t stage_bytes = 0;
+    hipEvent_t stage_done = nullptr;
+    bool stage_used = false;
     int grid_cap = 0;                 // work-group limit of state passes (0 = the kernels' own)
     std::vector<hipEvent_t> events;   // per-pass timing events of profiled runs (reused)
 };

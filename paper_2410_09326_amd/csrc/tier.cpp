@@ -129,7 +129,7 @@ static bool specialise(const LOp& o, uint64_t inactive, uint64_t val, const std:
         if (ident) return false;
         out.k = k2;
         for (int j = 0; j < k2; ++j) out.t[j] = pos[o.t[keep[j]]];
-        out.m.swap(tab);
+        out.m = tab;
         out.cphase = true;
         for (size_t i = 0; i + 1 < out.m.size(); ++i) out.cphase = out.cphase && out.m[i] == cd(1, 0);
         return true;
