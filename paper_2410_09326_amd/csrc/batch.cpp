@@ -34,6 +34,7 @@ struct qops_batch_exec {
         int kind = 0;                   // 0: register tiles (R, W), 1: LDS tiles
         int R = 0, W = 0;
         int lds = 0;                    // dynamic LDS bytes
+        bool whole = false;             // whole-state tiles: a branch of its own
         std::vector<BatchItem> items;
         BatchItem* d = nullptr;
     };
@@ -56,12 +57,22 @@ struct qops_batch_exec {
     char* d_states = nullptr;
     hipStream_t stream = nullptr;
     bool own_stream = false;
+    std::vector<hipStream_t> side;      // branches of whole-state nodes
+    std::vector<hipEvent_t> side_done;
+    hipEvent_t fork = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     double last_seconds = 0;
 };
 
 namespace {
+
+// Runs start to finish in the LDS kernel (the others run in tile passes, of
+// which a state in one register tile has one).
+bool lds_circuit(const qops_batch_exec* e, const Plan& p)
+{
+    return p.n <= e->small_max_n && (p.passes.empty() || p.passes[0].type == PASS_STATE_LDS);
+}
 
 int32_t plan_all(qops_batch_exec* e, const qops_batch* b)
 {
@@ -73,13 +84,17 @@ int32_t plan_all(qops_batch_exec* e, const qops_batch* b)
         par.state_lds_max_n = e->small_max_n;
         par.max_fuse_k = e->fuse_k;
         par.L_lds = std::min(e->tile_bits, n);
-        par.reg_up = std::min(e->tile_bits, n) - 6;   // register tiles of the same width
-        par.state_reg = 0;
+        // register tiles of the same width; a circuit that may run in one
+        // work-group and has no dense block is one register tile (a 13-qubit,
+        // depth-32 circuit of the sweep takes about 0.3 ms that way, 3 ms with
+        // every operation in LDS)
+        par.reg_up = (n <= e->small_max_n ? n : std::min(e->tile_bits, n)) - 6;
+        par.state_reg = n <= e->small_max_n ? n : 0;
         Err er = build_plan(n, b->precision, nullptr, b->gates[i], b->n_gates[i], par, e->plans[i]);
         if (!er.ok()) return set_error(er.code, "circuit " + std::to_string(i) + ": " + er.msg);
         const Plan& p = e->plans[i];
         for (const PassPlan& pp : p.passes) {
-            const bool ok = n <= e->small_max_n ? pp.type == PASS_STATE_LDS
+            const bool ok = n <= e->small_max_n ? pp.type == PASS_STATE_LDS || (pp.type == PASS_TILE_REG && pp.L == n)
                                                 : (pp.type == PASS_TILE_LDS || pp.type == PASS_TILE_REG);
             if (!ok)
                 return set_error(QOPS_UNSUPPORTED, "circuit " + std::to_string(i) +
@@ -119,7 +134,7 @@ void program_images(const qops_batch_exec* e, std::vector<PassHdr>& hdrs, std::v
                 if (pp.type == PASS_TILE_LDS && d.b) continue;
                 d.coef += coef_n;
             }
-        if (p.n <= e->small_max_n) continue;
+        if (lds_circuit(e, p)) continue;
         for (const PassPlan& pp : p.passes) {
             PassHdr h = p.hdrs[pp.hdr];
             h.op0 += op_base;
@@ -149,7 +164,7 @@ int32_t layout(qops_batch_exec* e)
         c.out0 = (int32_t)out0;
         out0 += p.n;
         e->coef_base[i] = coef_n;
-        if (p.n <= e->small_max_n) {
+        if (lds_circuit(e, p)) {
             c.op0 = (int32_t)op_n + (p.passes.empty() ? 0 : p.passes[0].op0);
             c.nops = p.passes.empty() ? 0 : p.passes[0].nops;
             c.npass = 0;
@@ -190,9 +205,10 @@ int32_t layout(qops_batch_exec* e)
             const PassHdr& h = p.hdrs[pp.hdr];
             const int kind = pp.type == PASS_TILE_REG ? 0 : 1;
             const int R = kind == 0 ? pp.R : 0, W = kind == 0 ? pp.W : 0;
+            const bool whole = p.n <= e->small_max_n;
             size_t at = first;
-            while (at < e->nodes.size() &&
-                   !(e->nodes[at].kind == kind && e->nodes[at].R == R && e->nodes[at].W == W))
+            while (at < e->nodes.size() && !(e->nodes[at].kind == kind && e->nodes[at].R == R &&
+                                             e->nodes[at].W == W && e->nodes[at].whole == whole))
                 ++at;
             if (at == e->nodes.size()) {
                 qops_batch_exec::Node nd;
@@ -200,6 +216,7 @@ int32_t layout(qops_batch_exec* e)
                 nd.kind = kind;
                 nd.R = R;
                 nd.W = W;
+                nd.whole = whole;
                 e->nodes.push_back(nd);
             }
             qops_batch_exec::Node& nd = e->nodes[at];
@@ -249,22 +266,60 @@ int32_t layout(qops_batch_exec* e)
     return QOPS_OK;
 }
 
+hipError_t enqueue_node(qops_batch_exec* e, const qops_batch_exec::Node& nd, hipStream_t s)
+{
+    // register-tile items: 6144 waves (six per SIMD, what the body's 66-76
+    // registers let reside) to hide the global loads and lane exchanges
+    if (nd.kind == 0)
+        return launch_batch_reg(e->prec, nd.R, nd.W, nd.d, (int)nd.items.size(), e->d_circs, e->d_hdrs, e->d_ops,
+                                e->d_coef, nd.pass, nd.lds, (e->grid * 12) >> nd.W, s);
+    return launch_batch_pass(e->prec, nd.d, (int)nd.items.size(), e->d_circs, e->d_hdrs, e->d_ops, e->d_coef, nd.pass,
+                             nd.lds, e->grid, s);
+}
+
+// The LDS circuits and the whole-state tiles are long programs on few
+// work-groups, so each of their kernels is a branch beside the tile passes of
+// the larger circuits (96 circuits of 10..20 qubits: 3.59 ms in one line,
+// 2.96 ms in branches); all join before the <Z> reduction.
 hipError_t enqueue(qops_batch_exec* e, hipStream_t s)
 {
-    hipError_t er = launch_batch_small(e->prec, e->d_small, (int)e->small_ids.size(), e->d_circs, e->d_ops, e->d_coef,
-                                       e->d_out, e->lds_small, s);
-    for (size_t k = 0; k < e->nodes.size() && er == hipSuccess; ++k) {
-        const auto& nd = e->nodes[k];
-        // register-tile items: 6144 one-wave work-groups (six per SIMD; as
-        // many as the body's registers let reside: three at 148 VGPRs with
-        // five register bits, six at 79-80 VGPRs with four) to hide the
-        // global loads and lane exchanges
-        if (nd.kind == 0)
-            er = launch_batch_reg(e->prec, nd.R, nd.W, nd.d, (int)nd.items.size(), e->d_circs, e->d_hdrs, e->d_ops,
-                                  e->d_coef, nd.pass, nd.lds, (e->grid * 12) >> nd.W, s);
-        else
-            er = launch_batch_pass(e->prec, nd.d, (int)nd.items.size(), e->d_circs, e->d_hdrs, e->d_ops, e->d_coef,
-                                   nd.pass, nd.lds, e->grid, s);
+    size_t used = 0;
+    auto branch = [&](hipStream_t& b) -> hipError_t {   // a stream that continues from s
+        if (e->side.size() == used) {
+            hipStream_t ns = nullptr;
+            hipEvent_t ev = nullptr;
+            hipError_t er = hipStreamCreateWithFlags(&ns, hipStreamNonBlocking);
+            if (er == hipSuccess && (er = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess)
+                (void)hipStreamDestroy(ns);
+            if (er != hipSuccess) return er;
+            e->side.push_back(ns);
+            e->side_done.push_back(ev);
+        }
+        b = e->side[used++];
+        return hipStreamWaitEvent(b, e->fork, 0);
+    };
+    hipError_t er = hipSuccess;
+    if (!e->fork) er = hipEventCreateWithFlags(&e->fork, hipEventDisableTiming);
+    if (er == hipSuccess) er = hipEventRecord(e->fork, s);
+    hipStream_t b = nullptr;
+    if (er == hipSuccess && !e->small_ids.empty()) {
+        er = branch(b);
+        if (er == hipSuccess)
+            er = launch_batch_small(e->prec, e->d_small, (int)e->small_ids.size(), e->d_circs, e->d_ops, e->d_coef,
+                                    e->d_out, e->lds_small, b);
+    }
+    for (size_t k = 0; k < e->nodes.size() && er == hipSuccess; ++k)
+        if (e->nodes[k].whole) {
+            er = branch(b);
+            if (er == hipSuccess) er = enqueue_node(e, e->nodes[k], b);
+        }
+    for (size_t k = 0; k < e->nodes.size() && er == hipSuccess; ++k)
+        if (!e->nodes[k].whole) er = enqueue_node(e, e->nodes[k], s);
+    // every branch joins, also after an error (a capture must not leave one open)
+    for (size_t k = 0; k < used; ++k) {
+        hipError_t ej = hipEventRecord(e->side_done[k], e->side[k]);
+        if (ej == hipSuccess) ej = hipStreamWaitEvent(s, e->side_done[k], 0);
+        if (er == hipSuccess) er = ej;
     }
     if (er == hipSuccess)
         er = launch_batch_z(e->prec, e->d_zitems, (int)e->z_items.size(), e->d_big, (int)e->big_ids.size(), e->d_circs,
@@ -282,6 +337,9 @@ void release(qops_batch_exec* e)
         if (p) (void)hipFree(p);
     for (auto& nd : e->nodes)
         if (nd.d) (void)hipFree(nd.d);
+    for (hipEvent_t ev : e->side_done) (void)hipEventDestroy(ev);
+    for (hipStream_t st : e->side) (void)hipStreamDestroy(st);
+    if (e->fork) (void)hipEventDestroy(e->fork);
     if (e->own_stream && e->stream) (void)hipStreamDestroy(e->stream);
 }
 
@@ -436,8 +494,8 @@ int32_t qops_batch_info(const qops_batch_exec* e, qops_batch_stats* s)
 {
     if (!e || !s) return set_error(QOPS_INVALID_ARG, "null argument");
     std::memset(s, 0, sizeof(*s));
-    s->small_circuits = (int32_t)e->small_ids.size();
-    s->tile_circuits = (int32_t)e->big_ids.size();
+    for (int i = 0; i < e->count; ++i) s->small_circuits += e->plans[i].n <= e->small_max_n ? 1 : 0;
+    s->tile_circuits = e->count - s->small_circuits;
     s->graph_nodes = (int32_t)(e->nodes.size() + (e->small_ids.empty() ? 0 : 1) + (e->big_ids.empty() ? 0 : 2));
     s->small_max_n = e->small_max_n;
     s->tile_bits = e->tile_bits;

@@ -1636,7 +1636,7 @@ static void pack(Plan& p)
     // a state of 10..12 qubits without dense blocks is one register tile (one
     // work-group): 12 qubits, 360 operations in complex128 take 199 us
     // against 611 with every operation reading and writing LDS
-    bool reg_state = p.par.state_reg && n >= 10 && n <= 12;
+    bool reg_state = n >= 10 && n <= p.par.state_reg;
     for (const LOp& o : p.lops) reg_state = reg_state && (o.kind == LOp::ONEQ || o.kind == LOp::DIAG);
     if (n <= p.par.state_lds_max_n && !reg_state) {
         // whole state in LDS; blocks the LDS kernel cannot take run as sweeps

@@ -102,7 +102,7 @@ struct PlanParams {
     int mode = QOPS_PLAN_FUSED;
     int swap_mode = QOPS_SWAP_VIRTUAL;
     int reg_up = 0;            // upper bits of register tiles (0 = by state size)
-    int state_reg = 1;         // small states without dense blocks run as one register tile
+    int state_reg = 12;        // states of 10 to this many qubits without dense blocks: one register tile (0 = off)
     int L_lds = 13;            // LDS-tile bits
     int max_fuse_k = 1;
     int use_mfma = 1;
