@@ -174,7 +174,8 @@ __device__ __forceinline__ void lds_put(V* lds, uint32_t off, const V& v)
     *reinterpret_cast<V*>(reinterpret_cast<unsigned char*>(lds) + off) = v;
 }
 
-template <int K, typename T>
+// NW: waves of the work-group.
+template <int K, typename T, int NW = 4>
 struct MfmaShape {
     // K = 3: the real embedding (2^(K+1) real rows, re/im interleaved).
     // K >= 4: Gauss's three-product form on complex rows: with U = A + iB
@@ -184,23 +185,24 @@ struct MfmaShape {
     static constexpr int KS = G ? 1 << (K - 2) : 1 << (K - 1);   // k-steps of 4 rows
     static constexpr int RB = G ? 1 << (K - 4) : 1 << (K - 3);   // row blocks of 16 rows
     static constexpr int RW = G ? RB : 1;                        // waves per column group
-    static constexpr int CW = 4 / RW;                            // column groups
+    static constexpr int CW = NW / RW;                           // column groups
     static constexpr int RPW = RB / RW;                          // row blocks per wave
     static constexpr int NF = G ? 3 : RPW;                       // fragment sets per wave
-    // column blocks in flight (one barrier per chunk if RW > 1)
-    static constexpr int CH = 4;
+    // column blocks in flight (one barrier per chunk if RW > 1); eight waves
+    // have two of a k >= 4 block's each on the 2^12 tile
+    static constexpr int CH = NW == 8 && G ? 2 : 4;
 };
 
 // The A fragments of a wave's row blocks (registers).
-template <int K, typename T>
-using MfmaFrag = T[MfmaShape<K, T>::NF][MfmaShape<K, T>::KS];
+template <int K, typename T, int NW = 4>
+using MfmaFrag = T[MfmaShape<K, T, NW>::NF][MfmaShape<K, T, NW>::KS];
 
 // The A fragments of the wave's row blocks, from global memory or LDS
 // (Gauss form: A, B and A + B of the wave's row block, per k-step).
-template <int K, typename T>
-__device__ __forceinline__ void mfma_load_a(MfmaFrag<K, T>& av, const T* __restrict__ A, int lane, int wave)
+template <int K, typename T, int NW = 4>
+__device__ __forceinline__ void mfma_load_a(MfmaFrag<K, T, NW>& av, const T* __restrict__ A, int lane, int wave)
 {
-    using S = MfmaShape<K, T>;
+    using S = MfmaShape<K, T, NW>;
     const int rg = wave % S::RW;
     if constexpr (S::G) {
 #pragma unroll
@@ -220,13 +222,18 @@ __device__ __forceinline__ void mfma_load_a(MfmaFrag<K, T>& av, const T* __restr
 // in k-step ks is input 4 ks + l/16 of column l%16, read as one (re, im)
 // pair; the result rows 4(l/16) + i, i < 4, of column l%16 come back in
 // registers i of the three accumulators.
-template <int K, typename T>
+// AREG: the A fragments are in registers (`av`); else they are read from
+// `al` one k-step ahead.  A wave that has one chunk of column blocks uses each
+// fragment once per operation, so reading it late costs nothing and a 6-qubit
+// complex128 block saves the 96 registers that would spill with eight waves.
+template <int K, typename T, int NW, bool AREG>
 __device__ __forceinline__ void mfma_core_gauss(typename CxT<T>::V* lds, int L, const DevOp& op,
-                                                const MfmaFrag<K, T>& av, int lane, int wave)
+                                                const MfmaFrag<K, T, NW>* av, const T* __restrict__ al, int lane,
+                                                int wave)
 {
     using V = typename CxT<T>::V;
     using A4 = typename CxT<T>::A4;
-    using S = MfmaShape<K, T>;
+    using S = MfmaShape<K, T, NW>;
     constexpr int KS = S::KS, RW = S::RW, CW = S::CW, CH = S::CH;
     const int rb = wave % RW, cg = wave / RW;
     const int ncb = 1 << (L - K - 4);
@@ -278,10 +285,20 @@ __device__ __forceinline__ void mfma_core_gauss(typename CxT<T>::V* lds, int L, 
         // so no MFMA waits on the vector ALU result it reads
         V bq[2][CH];
         T bs[2][CH];
+        T aq[2][3];
+        auto load_a = [&](auto kc, T* a) {
+            constexpr int ks = decltype(kc)::value;
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+                if constexpr (AREG) a[m] = (*av)[m][ks];
+                else a[m] = al[((rb * KS + ks) * 3 + m) * 64 + lane];
+            }
+        };
         sfor<CH>([&](auto cc) {
             constexpr int c = decltype(cc)::value;
             bq[0][c] = lds_at(lds, gin[c]);
         });
+        if constexpr (!AREG) load_a(std::integral_constant<int, 0>{}, aq[0]);
         sfor<CH>([&](auto cc) {
             constexpr int c = decltype(cc)::value;
             bs[0][c] = bq[0][c].x + bq[0][c].y;
@@ -295,13 +312,15 @@ __device__ __forceinline__ void mfma_core_gauss(typename CxT<T>::V* lds, int L, 
                     constexpr int c = decltype(cc)::value;
                     bq[cur ^ 1][c] = lds_at(lds, gin[c] ^ nx);
                 });
+                if constexpr (!AREG) load_a(std::integral_constant<int, ks + 1>{}, aq[cur ^ 1]);
             }
+            if constexpr (AREG) load_a(kc, aq[cur]);
             __builtin_amdgcn_sched_barrier(0);
             sfor<CH>([&](auto cc) {
                 constexpr int c = decltype(cc)::value;
-                d1[c] = mfma(av[0][ks], bq[cur][c].x, d1[c]);
-                d2[c] = mfma(av[1][ks], bq[cur][c].y, d2[c]);
-                d3[c] = mfma(av[2][ks], bs[cur][c], d3[c]);
+                d1[c] = mfma(aq[cur][0], bq[cur][c].x, d1[c]);
+                d2[c] = mfma(aq[cur][1], bq[cur][c].y, d2[c]);
+                d3[c] = mfma(aq[cur][2], bs[cur][c], d3[c]);
             });
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (ks + 1 < KS) {
@@ -331,17 +350,17 @@ __device__ __forceinline__ void mfma_core_gauss(typename CxT<T>::V* lds, int L, 
     __builtin_amdgcn_s_setprio(0);
 }
 
-template <int K, typename T>
-__device__ __forceinline__ void mfma_core(typename CxT<T>::V* lds, int L, const DevOp& op, const MfmaFrag<K, T>& av,
+template <int K, typename T, int NW = 4>
+__device__ __forceinline__ void mfma_core(typename CxT<T>::V* lds, int L, const DevOp& op, const MfmaFrag<K, T, NW>& av,
                                           int lane, int wave)
 {
-    if constexpr (MfmaShape<K, T>::G) {
-        mfma_core_gauss<K, T>(lds, L, op, av, lane, wave);
+    if constexpr (MfmaShape<K, T, NW>::G) {
+        mfma_core_gauss<K, T, NW, true>(lds, L, op, &av, nullptr, lane, wave);
         return;
     } else {
     using V = typename CxT<T>::V;
     using A4 = typename CxT<T>::A4;
-    using S = MfmaShape<K, T>;
+    using S = MfmaShape<K, T, NW>;
     constexpr int KS = S::KS, RW = S::RW, CW = S::CW, RPW = S::RPW, CH = S::CH;
     const int rg = wave % RW, cg = wave / RW;
     const int ncb = 1 << (L - K - 4);
@@ -610,13 +629,17 @@ __device__ __forceinline__ void mfma_core_wide(float2* lds, int L, const DevOp& 
     __builtin_amdgcn_s_setprio(0);
 }
 
-template <int K, typename T>
+template <int K, typename T, int NW = 4>
 __device__ void mfma_lds(typename CxT<T>::V* lds, int L, const DevOp& op, const T* __restrict__ A, int lane,
                          int wave)
 {
-    MfmaFrag<K, T> av;
-    mfma_load_a<K, T>(av, A, lane, wave);
-    mfma_core<K, T>(lds, L, op, av, lane, wave);
+    if constexpr (K == 6 && NW == 8) {
+        mfma_core_gauss<K, T, NW, false>(lds, L, op, nullptr, A, lane, wave);
+        return;
+    }
+    MfmaFrag<K, T, NW> av;
+    mfma_load_a<K, T, NW>(av, A, lane, wave);
+    mfma_core<K, T, NW>(lds, L, op, av, lane, wave);
 }
 
 // Matrix-core blocks of at most KMAX qubits (a kernel that keeps a larger
@@ -626,7 +649,7 @@ __device__ void mfma_lds(typename CxT<T>::V* lds, int L, const DevOp& op, const 
 // says which forms a kernel can meet, so that it compiles only those: 0 =
 // never the wide one, 1 = either, 2 = the wide one for every 5-qubit block
 // (complex64 on the largest tile).
-template <typename T, int KMAX = 6, int WCH = 2, int WMODE = 0>
+template <typename T, int KMAX = 6, int WCH = 2, int WMODE = 0, int NW = 4>
 __device__ void mfma_dispatch(typename CxT<T>::V* lds, int L, const DevOp& op, const T* __restrict__ A, int lane,
                               int wave)
 {
@@ -639,18 +662,18 @@ __device__ void mfma_dispatch(typename CxT<T>::V* lds, int L, const DevOp& op, c
     }
     if constexpr (WMODE == 2) {
         switch (op.a) {
-        case 3: mfma_lds<3, T>(lds, L, op, A, lane, wave); break;
-        case 4: mfma_lds<4, T>(lds, L, op, A, lane, wave); break;
-        case 6: if constexpr (KMAX >= 6) mfma_lds<6, T>(lds, L, op, A, lane, wave); break;
+        case 3: mfma_lds<3, T, NW>(lds, L, op, A, lane, wave); break;
+        case 4: mfma_lds<4, T, NW>(lds, L, op, A, lane, wave); break;
+        case 6: if constexpr (KMAX >= 6) mfma_lds<6, T, NW>(lds, L, op, A, lane, wave); break;
         default: break;
         }
         return;
     }
     switch (op.a) {
-    case 3: mfma_lds<3, T>(lds, L, op, A, lane, wave); break;
-    case 4: mfma_lds<4, T>(lds, L, op, A, lane, wave); break;
-    case 5: if constexpr (KMAX >= 5) mfma_lds<5, T>(lds, L, op, A, lane, wave); break;
-    case 6: if constexpr (KMAX >= 6) mfma_lds<6, T>(lds, L, op, A, lane, wave); break;
+    case 3: mfma_lds<3, T, NW>(lds, L, op, A, lane, wave); break;
+    case 4: mfma_lds<4, T, NW>(lds, L, op, A, lane, wave); break;
+    case 5: if constexpr (KMAX >= 5) mfma_lds<5, T, NW>(lds, L, op, A, lane, wave); break;
+    case 6: if constexpr (KMAX >= 6) mfma_lds<6, T, NW>(lds, L, op, A, lane, wave); break;
     default: break;
     }
 }
@@ -680,8 +703,15 @@ __device__ __forceinline__ uint64_t tile_base(uint64_t tile, const PassHdr* __re
     return base;
 }
 
-// Amplitudes per thread of the largest LDS tile (2^13 c64, 2^12 c128).
-template <typename T> constexpr int kLdsEpt = sizeof(T) == 4 ? 32 : 16;
+// Threads of the LDS tile kernel: complex64 runs two work-groups of four waves
+// per CU; complex128 fits one, which takes eight waves on the full tile so that
+// one wave's LDS reads and tile accesses run under another's MFMAs.  With that,
+// every coefficient read from LDS (an operation that may read global memory
+// waits for the next tile's loads), 24 complex128 blocks of 2, 3, 4, 5, 6
+// qubits take 0.42, 0.67, 0.78, 1.19, 2.18 ms at 23 qubits, with four waves
+// 0.56, 0.76, 0.92, 1.38, 2.70 ms; 60 mixed blocks of 26 qubits 18.2, 23.1 ms.
+template <typename T, bool FULL> constexpr int kLdsThreads = sizeof(T) == 8 && FULL ? 512 : 256;
+template <typename T, bool FULL> constexpr int kLdsEpt = (sizeof(T) == 4 ? 8192 : 4096) / kLdsThreads<T, FULL>;
 template <typename T> constexpr int kLdsTileBytes = sizeof(T) == 4 ? QOPS_LDS_TILE_BYTES_C64 : QOPS_LDS_TILE_BYTES_C128;
 
 // LDS tile pass, persistent and software-pipelined: a work-group stages the
@@ -699,12 +729,14 @@ template <typename T> constexpr int kLdsTileBytes = sizeof(T) == 4 ? QOPS_LDS_TI
 // the wait before the LDS fill covers the loads only: the stores drain under
 // the next tile's work.  Smaller tiles test each element and wait for all.
 template <typename T, int HK, bool FULL>
-__global__ void __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1)
+__global__ void __launch_bounds__((kLdsThreads<T, FULL>), sizeof(T) == 4 ? 2 : 1)
 tile_lds_kernel(typename CxT<T>::V* __restrict__ st, const PassHdr* __restrict__ hp, const DevOp* __restrict__ ops,
                 const T* __restrict__ coef, uint64_t ntiles)
 {
     using V = typename CxT<T>::V;
-    constexpr int EPT = kLdsEpt<T>;
+    constexpr int NT = kLdsThreads<T, FULL>, NW = NT / 64;
+    constexpr int TBITS = NT == 512 ? 9 : 8;       // bits of the thread number
+    constexpr int EPT = kLdsEpt<T, FULL>;          // amplitudes per thread of the largest tile
     // one static block at a known LDS address: the swizzled accesses of the
     // matrix-core loops then take one XOR each and no base add
     __shared__ __align__(16) unsigned char smem_raw[kLdsTileBytes<T>];
@@ -719,7 +751,7 @@ tile_lds_kernel(typename CxT<T>::V* __restrict__ st, const PassHdr* __restrict__
     T* lcoef = reinterpret_cast<T*>(smem_raw + ((size_t)N * sizeof(V)));
     {
         const T* __restrict__ src = coef + hp->coef_src;
-        for (int i = tid; i < hp->coef_n; i += 256) lcoef[i] = src[i];
+        for (int i = tid; i < hp->coef_n; i += NT) lcoef[i] = src[i];
     }
     constexpr int HKK = HK > 0 ? HK : 3;
     // the full complex64 tile keeps its hoisted block in the 32x32x2 layout
@@ -727,18 +759,18 @@ tile_lds_kernel(typename CxT<T>::V* __restrict__ st, const PassHdr* __restrict__
     // (a hoisted 5-qubit block keeps that form's fragments)
     constexpr bool WFULL = sizeof(T) == 4 && FULL;
     constexpr bool HWIDE = WFULL && HK == 5;
-    MfmaFrag<HKK, T> hav;
+    MfmaFrag<HKK, T, NW> hav;
     WideFrag<5> haw;
     const int hoist = HK > 0 ? hp->hoist : -1;
     if constexpr (HK > 0) {
         __syncthreads();   // staged coefficients visible
         const DevOp hop = prog[hoist];   // never staged: read from global memory once
         if constexpr (HWIDE) wide_load_a<5>(haw, reinterpret_cast<const float*>(coef) + hop.coef, lane, wave);
-        else mfma_load_a<HKK, T>(hav, coef + hop.coef, lane, wave);
+        else mfma_load_a<HKK, T, NW>(hav, coef + hop.coef, lane, wave);
     }
-    // element e = 256 u + tid: bits 0..F-1 of tid are physical bits 0..F-1
-    // (F = QOPS_LDS_FIXED_BITS, contiguous in memory), bits F..7 of tid
-    // select up_phys[0 .. 7-F], bit b of u selects up_phys[8-F+b].
+    // element e = NT u + tid: bits 0..F-1 of tid are physical bits 0..F-1
+    // (F = QOPS_LDS_FIXED_BITS, contiguous in memory), its TBITS - F others
+    // select up_phys[0 ..], bit b of u selects up_phys[TBITS-F+b].
     // P2 (full complex64 tiles): each thread moves two adjacent amplitudes
     // with one 16-byte access, element e = 512 u + 2 tid + h: h and bits
     // 0..F-2 of tid are physical bits 0..F-1, bits F-1..7 of tid select
@@ -749,8 +781,8 @@ tile_lds_kernel(typename CxT<T>::V* __restrict__ st, const PassHdr* __restrict__
     constexpr bool P2 = FULL && sizeof(T) == 4;
     constexpr int NU = P2 ? EPT / 2 : EPT;         // accesses per thread and tile
     constexpr int TB = P2 ? F - 1 : F;              // tid bits inside the contiguous run
-    constexpr int UB0 = P2 ? 9 - F : 8 - F;         // up_phys index of u's bit 0
-    constexpr int NUB = P2 ? 4 : 5;                 // bits of u
+    constexpr int UB0 = P2 ? 9 - F : TBITS - F;     // up_phys index of u's bit 0
+    constexpr int NUB = NU == 8 ? 3 : (NU == 16 ? 4 : 5);   // bits of u
     const uint32_t tlow = ((uint32_t)tid & ((1u << TB) - 1u)) << (P2 ? 1 : 0);
     const uint64_t dep_thr = dep_up((uint32_t)(tid >> TB), hp->up_phys, nup);
     uint64_t ub[NUB];
@@ -777,7 +809,7 @@ tile_lds_kernel(typename CxT<T>::V* __restrict__ st, const PassHdr* __restrict__
             constexpr int u = decltype(uc)::value;
             if constexpr (P2) {
                 q2[u] = *reinterpret_cast<const float4*>(src + uoff(u));
-            } else if (FULL || 256u * u < N) {
+            } else if (FULL || (uint32_t)NT * u < N) {
                 const V x = src[uoff(u)];
                 pr[u] = x.x;
                 pi[u] = x.y;
@@ -801,11 +833,11 @@ tile_lds_kernel(typename CxT<T>::V* __restrict__ st, const PassHdr* __restrict__
                 w.z = pswap ? x.x : x.z;
                 w.w = pswap ? x.y : x.w;
                 lds_put(reinterpret_cast<float4*>(smem_raw), (swz(512u * u) ^ psw) * 8u, w);
-            } else if (FULL || 256u * u < N) {
+            } else if (FULL || (uint32_t)NT * u < N) {
                 V x;
                 x.x = pr[u];
                 x.y = pi[u];
-                lds[swz(256u * u) ^ tsw] = x;
+                lds[swz((uint32_t)NT * u) ^ tsw] = x;
             }
         });
         __syncthreads();
@@ -813,15 +845,12 @@ tile_lds_kernel(typename CxT<T>::V* __restrict__ st, const PassHdr* __restrict__
         for (int i = 0; i < nops; ++i) {
             const DevOp op = prog[i];
             if ((base & op.c_glob) != op.c_glob) continue;
-            // complex64 passes hold every coefficient except the hoisted
-            // block's in LDS (the planner guarantees it), so their ops issue
-            // no vector-memory loads and never wait on the next tile's loads
-            // in flight; complex128 ops read from LDS (op.b = 1) or global
-            const T* cf;
-            if constexpr (sizeof(T) == 4) cf = lcoef + op.coef;
-            else cf = op.b ? lcoef + op.coef : coef + op.coef;
+            // every coefficient except the hoisted block's is in LDS (the
+            // planner guarantees it), so the ops issue no vector-memory
+            // loads and never wait on the next tile's loads in flight
+            const T* cf = lcoef + op.coef;
             if (op.type == OP_DENSE_LDS) {
-                dense_lds_dispatch<T>(lds, L, op, cf, tid, 256);
+                dense_lds_dispatch<T>(lds, L, op, cf, tid, NT);
             } else if (op.type == OP_MFMA) {
                 if constexpr (HWIDE) {
                     if (i == hoist) mfma_core_wide<5, 1, true>(lds, L, op, &haw, nullptr, lane, wave);
@@ -829,18 +858,18 @@ tile_lds_kernel(typename CxT<T>::V* __restrict__ st, const PassHdr* __restrict__
                 } else if constexpr (WFULL && HK > 0) {
                     // beside a hoisted 6-qubit block, one column block of the
                     // 5-qubit ones in flight
-                    if (i == hoist) mfma_core<HKK, T>(lds, L, op, hav, lane, wave);
+                    if (i == hoist) mfma_core<HKK, T, NW>(lds, L, op, hav, lane, wave);
                     else mfma_dispatch<T, 5, 1, 2>(lds, L, op, cf, lane, wave);
                 } else if constexpr (HK > 0) {
-                    if (i == hoist) mfma_core<HKK, T>(lds, L, op, hav, lane, wave);
+                    if (i == hoist) mfma_core<HKK, T, NW>(lds, L, op, hav, lane, wave);
                     else mfma_dispatch<T, 5>(lds, L, op, cf, lane, wave);
                 } else if constexpr (WFULL) {
                     mfma_dispatch<T, 6, 2, 2>(lds, L, op, cf, lane, wave);
                 } else {
-                    mfma_dispatch<T>(lds, L, op, cf, lane, wave);
+                    mfma_dispatch<T, 6, 2, 0, NW>(lds, L, op, cf, lane, wave);
                 }
             } else if (op.type == OP_DIAG_LDS) {
-                diag_lds<T>(lds, L, op, cf, base, tid, 256);
+                diag_lds<T>(lds, L, op, cf, base, tid, NT);
             }
             __syncthreads();
         }
@@ -856,8 +885,8 @@ tile_lds_kernel(typename CxT<T>::V* __restrict__ st, const PassHdr* __restrict__
                     w.z = pswap ? x.x : x.z;
                     w.w = pswap ? x.y : x.w;
                     *reinterpret_cast<float4*>(dst + uoff(u)) = w;
-                } else if (FULL || 256u * u < N) {
-                    dst[uoff(u)] = lds[swz(256u * u) ^ tsw];
+                } else if (FULL || (uint32_t)NT * u < N) {
+                    dst[uoff(u)] = lds[swz((uint32_t)NT * u) ^ tsw];
                 }
             });
         }
@@ -885,7 +914,7 @@ static hipError_t launch_tile_lds_f(void* state, const PassHdr* hdr, const DevOp
 {
     using V = typename CxT<T>::V;
     (void)lds_bytes;   // checked against the kernel's static block by the caller
-    hipLaunchKernelGGL((tile_lds_kernel<T, HK, FULL>), dim3((unsigned)grid), dim3(256), 0, s,
+    hipLaunchKernelGGL((tile_lds_kernel<T, HK, FULL>), dim3((unsigned)grid), dim3(kLdsThreads<T, FULL>), 0, s,
                        reinterpret_cast<V*>(state), hdr, ops, reinterpret_cast<const T*>(coef), ntiles);
     return hipGetLastError();
 }
@@ -894,7 +923,7 @@ template <typename T, int HK>
 static hipError_t launch_tile_lds_t(void* state, const PassHdr* hdr, const DevOp* ops, const void* coef,
                                     uint64_t grid, uint64_t ntiles, int L, int lds_bytes, hipStream_t s)
 {
-    constexpr int LMAX = sizeof(T) == 4 ? 13 : 12;   // 256 threads x kLdsEpt<T>
+    constexpr int LMAX = sizeof(T) == 4 ? 13 : 12;   // kLdsThreads x kLdsEpt amplitudes
     if (L == LMAX) return launch_tile_lds_f<T, HK, true>(state, hdr, ops, coef, grid, ntiles, lds_bytes, s);
     return launch_tile_lds_f<T, HK, false>(state, hdr, ops, coef, grid, ntiles, lds_bytes, s);
 }

@@ -1821,18 +1821,21 @@ static Err finish_plan(Plan& p, std::vector<LOp>& lowered, std::chrono::steady_c
     }
     pack(p);
     // LDS tile kernels start each of their 256 threads on a distinct tile
-    // element (tiles of at least 2^8); complex64 ones read every coefficient
-    // but the hoisted block's from LDS, so each such op must be staged
-    for (const PassPlan& pp : p.passes)
-        if (pp.type == PASS_TILE_LDS && pp.L < 8)
-            return mkerr(QOPS_UNSUPPORTED, "internal: LDS tile of fewer than 2^8 amplitudes");
+    // element (tiles of at least 2^8; 512 threads only on the largest
+    // complex128 tile) and read every coefficient but the hoisted block's from
+    // LDS, so each such op must be staged
+    for (const PassPlan& pp : p.passes) {
+        if (pp.type != PASS_TILE_LDS) continue;
+        if (pp.L < 8) return mkerr(QOPS_UNSUPPORTED, "internal: LDS tile of fewer than 2^8 amplitudes");
+        const PassHdr& h = p.hdrs[pp.hdr];
+        for (int i = h.op0; i < h.op0 + h.nops; ++i)
+            if (i - h.op0 != h.hoist && !p.dops[i].b)
+                return mkerr(QOPS_UNSUPPORTED, "internal: an LDS-pass operation could not be staged");
+    }
     if (p.prec == 0)
         for (const PassPlan& pp : p.passes) {
             if (pp.type != PASS_TILE_LDS) continue;
             const PassHdr& h = p.hdrs[pp.hdr];
-            for (int i = h.op0; i < h.op0 + h.nops; ++i)
-                if (i - h.op0 != h.hoist && !p.dops[i].b)
-                    return mkerr(QOPS_UNSUPPORTED, "internal: an LDS-pass operation could not be staged");
             // the kernel keeps one block of 5 or 6 qubits in registers and
             // runs the others through the 5-qubit dispatch: a second block as
             // wide as 6 would be skipped there, so it must never reach it
