@@ -67,25 +67,27 @@ enum RegCode : int32_t {
     RC_X_REG = 8,          // + 3 register bit; + 1, + 2 as above
     RC_1Q_REG = 23,        // + 3 register bit; + 1, + 2 as above
     RC_SHEAR_REG = 38,     // + 6 register bit + 3 form + type (0 complex, 1 real, 2 imaginary)
-    RC_SHEAR_LANE = 68,    // + 6 lane bit + 3 exchanged + type
+    RC_SHEAR_LANE = 68,    // + 6 lane bit (0..3) + 3 exchanged + type
+    RC_SHEAR_ROW = 92,     // + 12 (lane bit - 4) + 6 exchanged + 3 form + type; exchanged ones leave
+                           //   the slots of register bit 0 exchanged
     // diagonal tables, coef: table, pos: sources of its index bits; aux = m |
     // first index << 8 | index bits of the register bits << 16 (3 bits each)
-    RC_DIAG = 104,         // any register bits
-    RC_DIAG0 = 105,        // none
-    RC_DIAG1 = 106,        // + register bit
-    RC_DIAG2 = 111,        // + pair number
+    RC_DIAG = 116,         // any register bits
+    RC_DIAG0 = 117,        // none
+    RC_DIAG1 = 118,        // + register bit
+    RC_DIAG2 = 123,        // + pair number
     // phase k[0] (sign: -1) where every masked bit is 1
-    RC_PHASE = 121,        // any register bits
-    RC_PHASE0 = 122,       // none
-    RC_PHASE1 = 123,       // + 2 register bit + required slot value
-    RC_PHASE2 = 133,       // + 4 pair number + required slot values (bit 0: lower register bit)
-    RC_SIGN = 173,         // as RC_PHASE
-    RC_SIGN0 = 174,
-    RC_SIGN1 = 175,
-    RC_SIGN2 = 185,
-    RC_CX_REG = 225,       // X on a register bit where another holds a value (no other control):
+    RC_PHASE = 133,        // any register bits
+    RC_PHASE0 = 134,       // none
+    RC_PHASE1 = 135,       // + 2 register bit + required slot value
+    RC_PHASE2 = 145,       // + 4 pair number + required slot values (bit 0: lower register bit)
+    RC_SIGN = 185,         // as RC_PHASE
+    RC_SIGN0 = 186,
+    RC_SIGN1 = 187,
+    RC_SIGN2 = 197,
+    RC_CX_REG = 237,       // X on a register bit where another holds a value (no other control):
                            // + 2 (2 pair number + (1: the target is the higher one)) + required value
-    RC_COUNT = 265
+    RC_COUNT = 277
 };
 
 template <typename T>

@@ -1233,7 +1233,13 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
                 Cl w, v;
                 int form, fl = 0;
                 ch.waits[b] = true;
-                if (lane) {
+                if (lane && b >= 4) {
+                    // the kernel pairs the lanes' rows through register bit 0,
+                    // whose slots an exchanged form leaves exchanged
+                    shear_reg_form(N, form, fl, w, v, ch.d0[b], ch.d1[b]);
+                    flip ^= (uint32_t)fl;
+                    d.code = RC_SHEAR_ROW + 12 * (b - 4) + 6 * fl + 3 * form + coef_type(w, v);
+                } else if (lane) {
                     shear_lane_form(N, form, w, v, ch.d0[b], ch.d1[b]);
                     d.code = RC_SHEAR_LANE + 6 * b + 3 * form + coef_type(w, v);
                 } else {

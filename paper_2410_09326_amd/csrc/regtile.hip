@@ -297,29 +297,90 @@ __device__ __forceinline__ void oneq_lane(int t, int lane, V (&a)[1 << R], V m00
     pin_tile(a);
 }
 
-// Value of lane ^ 2^BIT.  Bits 0, 1 and 3 are DPP moves inside a row of 16
-// lanes (quad permutes; a rotation by 8), which cost one vector move and no
-// LDS traffic; the others go through ds_bpermute.
+// Value of lane ^ 2^BIT, BIT < 4: DPP moves inside a row of 16 lanes (quad
+// permutes; a mirrored half row, ^ 7, and a reversed quad, ^ 3; a rotation by
+// 8), which cost one or two vector moves, no LDS traffic and no wait (bit 2
+// was an LDS permute: 0.27 -> 0.24 us a complex64 operation at 13 qubits).
 template <int BIT>
-__device__ __forceinline__ int lane_xor_i(int v, int addr)
+__device__ __forceinline__ int lane_xor_i(int v)
 {
     if constexpr (BIT == 0) return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xf, 0xf, true);
     else if constexpr (BIT == 1) return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xf, 0xf, true);
     else if constexpr (BIT == 3) return __builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, true);
-    else return __builtin_amdgcn_ds_bpermute(addr, v);
+    else return __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(v, 0x141, 0xf, 0xf, true), 0x1B, 0xf, 0xf, true);
 }
 template <int BIT>
-__device__ __forceinline__ float lane_xor(float v, int addr)
+__device__ __forceinline__ float lane_xor(float v)
 {
-    return __int_as_float(lane_xor_i<BIT>(__float_as_int(v), addr));
+    return __int_as_float(lane_xor_i<BIT>(__float_as_int(v)));
 }
 template <int BIT>
-__device__ __forceinline__ double lane_xor(double v, int addr)
+__device__ __forceinline__ double lane_xor(double v)
 {
     const long long b = __double_as_longlong(v);
-    const int lo = lane_xor_i<BIT>((int)(b & 0xffffffffll), addr);
-    const int hi = lane_xor_i<BIT>((int)(b >> 32), addr);
+    const int lo = lane_xor_i<BIT>((int)(b & 0xffffffffll));
+    const int hi = lane_xor_i<BIT>((int)(b >> 32));
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Exchanges the odd rows (of 16 lanes, BIT = 4, or 32, BIT = 5) of x with the
+// even rows of y, in place.
+template <int BIT>
+__device__ __forceinline__ void swap_rows(uint32_t& x, uint32_t& y)
+{
+    if constexpr (BIT == 4) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+        x = r[0];
+        y = r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        x = r[0];
+        y = r[1];
+    }
+}
+template <int BIT>
+__device__ __forceinline__ void swap_rows(float& x, float& y)
+{
+    uint32_t a = __float_as_uint(x), b = __float_as_uint(y);
+    swap_rows<BIT>(a, b);
+    x = __uint_as_float(a);
+    y = __uint_as_float(b);
+}
+template <int BIT>
+__device__ __forceinline__ void swap_rows(double& x, double& y)
+{
+    const unsigned long long p = (unsigned long long)__double_as_longlong(x),
+                             q = (unsigned long long)__double_as_longlong(y);
+    uint32_t pl = (uint32_t)p, ph = (uint32_t)(p >> 32), ql = (uint32_t)q, qh = (uint32_t)(q >> 32);
+    swap_rows<BIT>(pl, ql);
+    swap_rows<BIT>(ph, qh);
+    x = __longlong_as_double((long long)((unsigned long long)ph << 32 | pl));
+    y = __longlong_as_double((long long)((unsigned long long)qh << 32 | ql));
+}
+
+// Scaled form of a 2x2 on lane bit 4 or 5.  The two slots of a pair (register
+// bit 0) swap rows, so that one holds the amplitudes with the bit 0 of both
+// and the other those with the bit 1: then it is shear_reg_b with the same
+// coefficients for every lane, and the rows are swapped back: two vector
+// instructions a pair and word where each slot had an LDS permute and its wait.
+// A u3 and a CZ on bits 4 and 5, mean of the two: complex128 0.34 -> 0.25 us at
+// 13 qubits and 21.0 -> 14.7 us at 26; complex64 0.29 -> 0.23 us and, at 27
+// qubits, 20.7 -> 17.2 us.
+// EX: slot 0 ends as bit value 1; swapping back in the other order puts the
+// amplitudes right and leaves the pair's slots exchanged (the planner's flip).
+template <int BIT, int R, bool EX, int FORM, int TY, typename T, typename V>
+__device__ __forceinline__ void shear_row_b(V (&a)[1 << R], T wr, T wi, T vr, T vi)
+{
+    sfor<(1 << R) / 2>([&](auto jc) {
+        constexpr int j = 2 * decltype(jc)::value, jp = j + FORM, jq = j + 1 - FORM;
+        swap_rows<BIT>(a[j].x, a[j + 1].x);
+        swap_rows<BIT>(a[j].y, a[j + 1].y);
+        axpy<TY>(a[jp], wr, wi, a[jq]);
+        axpy<TY>(a[jq], vr, vi, a[jp]);
+        swap_rows<BIT>(a[j + EX].x, a[j + 1 - EX].x);
+        swap_rows<BIT>(a[j + EX].y, a[j + 1 - EX].y);
+    });
+    pin_tile(a);
 }
 
 // Scaled form of a 2x2 on lane bit BIT: the lane's amplitude plus W times its
@@ -331,12 +392,11 @@ __device__ __forceinline__ void shear_lane_b(int lane, V (&a)[1 << R], T wr, T w
 {
     const bool hi = (lane >> BIT) & 1;
     const T cr = hi ? vr : wr, ci = hi ? vi : wi;
-    const int addr = (lane ^ (1 << BIT)) << 2;
     sfor<(1 << R)>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
         V p;
-        p.x = lane_xor<BIT>(a[j].x, addr);
-        p.y = lane_xor<BIT>(a[j].y, addr);
+        p.x = lane_xor<BIT>(a[j].x);
+        p.y = lane_xor<BIT>(a[j].y);
         if constexpr (EX && TY == 0) {
             // p + c a into a: both products with a.x before a.x is replaced
             const T t = fmat(cr, a[j].x, p.x), u = fmat(ci, a[j].x, p.y);
@@ -554,6 +614,12 @@ __device__ __forceinline__ void reg_tile(typename CxT<T>::V* __restrict__ st, co
 #define QOPS_LANE_CASES(B)                                                                                   \
     QOPS_LANE_CASE(B, 0, 0) QOPS_LANE_CASE(B, 0, 1) QOPS_LANE_CASE(B, 0, 2)                                  \
     QOPS_LANE_CASE(B, 1, 0) QOPS_LANE_CASE(B, 1, 1) QOPS_LANE_CASE(B, 1, 2)
+#define QOPS_ROW_CASE(B, EX, F, TY)                                                                          \
+    QOPS_CASE_IF(RC_SHEAR_ROW + 12 * (B - 4) + 6 * EX + 3 * F + TY, true,                                    \
+                 (shear_row_b<B, R, EX != 0, F, TY>(a, op.k[0], op.k[1], op.k[2], op.k[3])))
+#define QOPS_ROW_CASES(B, EX)                                                                                \
+    QOPS_ROW_CASE(B, EX, 0, 0) QOPS_ROW_CASE(B, EX, 0, 1) QOPS_ROW_CASE(B, EX, 0, 2)                         \
+    QOPS_ROW_CASE(B, EX, 1, 0) QOPS_ROW_CASE(B, EX, 1, 1) QOPS_ROW_CASE(B, EX, 1, 2)
 #define QOPS_LANE_1Q(C)                                                                                      \
     QOPS_CASE_IF(RC_X_LANE + C, true, (xgate_lane<R, C>(op.aux, lane, a, creg, cval, C ? tok_of() : true)))  \
     QOPS_CASE_IF(RC_1Q_LANE + C, true, V m[4]; full(m);                                                      \
@@ -564,7 +630,8 @@ __device__ __forceinline__ void reg_tile(typename CxT<T>::V* __restrict__ st, co
             QOPS_PAIR_CASES(1, 3) QOPS_PAIR_CASES(2, 3) QOPS_PAIR_CASES(0, 4) QOPS_PAIR_CASES(1, 4)
             QOPS_PAIR_CASES(2, 4) QOPS_PAIR_CASES(3, 4)
             QOPS_LANE_CASES(0) QOPS_LANE_CASES(1) QOPS_LANE_CASES(2)
-            QOPS_LANE_CASES(3) QOPS_LANE_CASES(4) QOPS_LANE_CASES(5)
+            QOPS_LANE_CASES(3)
+            QOPS_ROW_CASES(4, 0) QOPS_ROW_CASES(4, 1) QOPS_ROW_CASES(5, 0) QOPS_ROW_CASES(5, 1)
             QOPS_LANE_1Q(0) QOPS_LANE_1Q(1) QOPS_LANE_1Q(2)
             QOPS_COND_CASES(true, RC_SIGN0, RC_PHASE0, 0u, 0u)
             QOPS_CASE_IF(RC_DIAG0, true, (phase_slots<R, 0u, 0u>(a, ldc(tab_of(), (int)ithr_of()))))

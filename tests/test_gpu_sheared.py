@@ -113,3 +113,31 @@ def test_every_register_condition(q, prec, tol, n, tile_upper):
     got = sim.state().astype(np.complex128)
     sim.close()
     assert np.max(np.abs(got - orc.run_circuit(circ))) <= tol
+
+
+@pytest.mark.parametrize("prec,tol", [(0, 2e-5), (1, 1e-12)])
+@pytest.mark.parametrize("n,tile_upper", [(10, 0), (13, 0), (14, 4), (14, 5), (14, 6), (14, 7)])
+@pytest.mark.parametrize("kind", ["u3", "ry", "rx"])
+def test_row_swaps(q, prec, tol, n, tile_upper, kind):
+    """2x2s on lane bits 2..5 alone and on register bits between them: each
+    order and exchange of the row-swapped form (angles on both sides of the
+    pivot boundary), the slots it leaves exchanged read by controls, phases,
+    X, RZZ and remaps."""
+    rng = np.random.default_rng(10 * n + tile_upper)
+    g = [W.Gate("h", (b,)) for b in range(n)]
+    for i in range(30):
+        for b in (2, 3, 4, 5):
+            th = float((0.4, 2.7, np.pi, -2.0, 0.0, 4.4)[int(rng.integers(6))])
+            g.append(W.Gate(kind, (b,), (), (th, *map(float, rng.uniform(0, 6.28, 2))) if kind == "u3" else (th,)))
+        b, c = (int(v) for v in rng.choice(np.arange(4, n), 2, replace=False))
+        k = ("cz", "cx", "cp", "rzz", "x")[i % 5]
+        g.append(W.Gate(k, (b,) if k == "x" else (b, c), (), (0.9,) if k in ("cp", "rzz") else ()))
+        if i % 4 == 0:
+            g.append(W.Gate("u3", (int(rng.integers(6, n)),), (), (float(rng.uniform(0, 6.28)), 0.3, 1.2)))
+    circ = W.Circuit(n, g, x0=3)
+    sim = q.Simulator(n, prec)
+    sim.init_basis(circ.x0)
+    sim.run(q.Plan(n, circ.gates, precision=prec, tile_upper=tile_upper))
+    got = sim.state().astype(np.complex128)
+    sim.close()
+    assert np.max(np.abs(got - orc.run_circuit(circ))) <= tol
