@@ -24,6 +24,14 @@ enum OpType : int32_t {
 enum BitSrc : int32_t { SRC_LANE = 0, SRC_WAVE = 1, SRC_REG = 2, SRC_GLOB = 3 };
 __host__ __device__ inline int32_t enc_src(int32_t cls, int32_t v) { return (cls << 8) | v; }
 
+// Source of a table index bit in a register tile pass, 13 bits: bit t of the
+// thread number (t | 32) or bit g of the tile's base index (g << 6 | 4096), so
+// that one expression reads either; 0: the bit is 0.
+__host__ __device__ inline int32_t enc_bit(int32_t cls, int32_t v)
+{
+    return cls == SRC_LANE ? v | 32 : cls == SRC_WAVE ? (6 + v) | 32 : cls == SRC_GLOB ? v << 6 | 4096 : 0;
+}
+
 struct DevOp {              // 64 bytes
     int32_t type;
     int32_t a;
@@ -70,8 +78,10 @@ enum RegCode : int32_t {
     RC_SHEAR_LANE = 68,    // + 6 lane bit (0..3) + 3 exchanged + type
     RC_SHEAR_ROW = 92,     // + 12 (lane bit - 4) + 6 exchanged + 3 form + type; exchanged ones leave
                            //   the slots of register bit 0 exchanged
-    // diagonal tables, coef: table, pos: sources of its index bits; aux = m |
-    // first index << 8 | index bits of the register bits << 16 (3 bits each)
+    // diagonal tables of 3 to 6 bits, coef: table, pos: sources (enc_bit) of
+    // its index bits; aux = m | first index << 8 | index bits of the register
+    // bits << 16 (3 bits each); RC_DIAG: ctl = index masks of register bits
+    // 0..3 (8 bits each)
     RC_DIAG = 116,         // any register bits
     RC_DIAG0 = 117,        // none
     RC_DIAG1 = 118,        // + register bit
@@ -87,7 +97,12 @@ enum RegCode : int32_t {
     RC_SIGN2 = 197,
     RC_CX_REG = 237,       // X on a register bit where another holds a value (no other control):
                            // + 2 (2 pair number + (1: the target is the higher one)) + required value
-    RC_COUNT = 277
+    // diagonal tables of at most 2 bits, entries k[0..3] by (bit 1, bit 0);
+    // aux: sources of the bits that are no register bits, bit 1's << 13
+    RC_TAB0 = 277,         // no register bit
+    RC_TAB1 = 278,         // + register bit, which is bit 1
+    RC_TAB2 = 283,         // + pair number, the lower register bit is bit 0
+    RC_COUNT = 293
 };
 
 template <typename T>

@@ -1296,34 +1296,55 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
             pp.flops += 6.0 * std::ldexp(1.0, p.n - o.k);
         } else {   // DIAG
             int nreg = 0, rbit[6] = {0}, tbit[6] = {0};   // register bits and their table bits
-            d.aux = o.k;
-            d.npos = o.k;
+            uint32_t first = 0;                           // table index of register slot 0
+            int32_t src[6] = {0};
             for (int j = 0; j < o.k; ++j) {
-                const int b = o.t[j];
+                const int b = o.t[j], u = b < 6 ? -1 : upos(b);
                 if (b < 6) {
-                    d.pos[j] = enc_src(SRC_LANE, b);
-                    continue;
-                }
-                const int u = upos(b);
-                if (u < 0) d.pos[j] = enc_src(SRC_GLOB, b);
-                else if (regbit(u) >= 0) {
-                    d.pos[j] = enc_src(SRC_REG, regbit(u));
-                    if (flip >> regbit(u) & 1u) d.aux |= 256 << j;
+                    src[j] = enc_bit(SRC_LANE, b);
+                } else if (u < 0) {
+                    src[j] = enc_bit(SRC_GLOB, b);
+                } else if (regbit(u) >= 0) {
+                    if (flip >> regbit(u) & 1u) first |= 1u << j;
                     rbit[nreg] = regbit(u);
                     tbit[nreg++] = j;
                 } else {
-                    d.pos[j] = enc_src(SRC_WAVE, wavebit(u));
+                    src[j] = enc_bit(SRC_WAVE, wavebit(u));
                 }
             }
             if (nreg == 2 && rbit[0] > rbit[1]) {
                 std::swap(rbit[0], rbit[1]);
                 std::swap(tbit[0], tbit[1]);
             }
-            d.code = nreg == 0 ? (int)RC_DIAG0
-                     : nreg == 1 ? RC_DIAG1 + rbit[0]
-                     : nreg == 2 ? RC_DIAG2 + pair_no(rbit[0], rbit[1]) : (int)RC_DIAG;
-            d.aux |= tbit[0] << 16 | tbit[1] << 19;
-            d.coef = push_coef(p, o.m);
+            if (o.k <= 2) {
+                // table bits in the record's order: a register bit last, two
+                // in ascending order (a 1-bit table has a second bit of 0)
+                const int hi = nreg ? tbit[nreg - 1] : o.k - 1, lo = o.k == 2 ? 1 - hi : -1;
+                cd e[4];
+                for (uint32_t i = 0; i < 4; ++i) {
+                    const uint32_t idx = (i >> 1) << hi | (lo >= 0 ? (i & 1u) << lo : 0u);
+                    e[i] = o.m[idx ^ first];
+                }
+                d.set({e[0], e[1], e[2], e[3]});
+                d.aux = (lo >= 0 ? src[lo] : 0) | src[hi] << 13;
+                d.code = nreg == 0 ? (int)RC_TAB0 : nreg == 1 ? RC_TAB1 + rbit[0] : RC_TAB2 + pair_no(rbit[0], rbit[1]);
+            } else {
+                d.npos = o.k;
+                for (int j = 0; j < o.k; ++j) d.pos[j] = src[j];
+                d.code = nreg == 0 ? (int)RC_DIAG0
+                         : nreg == 1 ? RC_DIAG1 + rbit[0]
+                         : nreg == 2 ? RC_DIAG2 + pair_no(rbit[0], rbit[1]) : (int)RC_DIAG;
+                d.aux = o.k | (int32_t)(first << 8) | tbit[0] << 16 | tbit[1] << 19;
+                if (nreg > 2) {
+                    uint32_t mask[4] = {0};
+                    for (int q = 0; q < nreg; ++q) mask[rbit[q]] = 1u << tbit[q];
+                    d.c_lane = mask[0];
+                    d.c_wave = mask[1];
+                    d.c_reg = mask[2];
+                    d.c_val = mask[3];
+                }
+                d.coef = push_coef(p, o.m);
+            }
             pp.n_diag_ops++;
             pp.flops += 6.0 * std::ldexp(1.0, p.n);
         }

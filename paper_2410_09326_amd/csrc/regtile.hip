@@ -170,6 +170,24 @@ __device__ __forceinline__ void phase_slots(V (&a)[1 << R], const V ph)
     pin_tile(a);
 }
 
+// Slots times the table entry of their register bits MA, MB (0: none):
+// p0, p1 (MA set), p2 (MB set), p3 (both).  Tables of at most two bits carry
+// their entries in the record: fetched through the vector cache they cost an
+// RZZ and a RY on register bits 0.62 us an operation at 20 qubits (complex64),
+// now 0.34.
+template <int R, uint32_t MA, uint32_t MB, typename V>
+__device__ __forceinline__ void mul_slots(V (&a)[1 << R], const V p0, const V p1, const V p2, const V p3)
+{
+    sfor<(1 << R)>([&](auto jc) {
+        constexpr uint32_t j = decltype(jc)::value;
+        if constexpr ((j & MA) && (j & MB)) cmul_to(a[j], p3);
+        else if constexpr ((j & MB) != 0u) cmul_to(a[j], p2);
+        else if constexpr ((j & MA) != 0u) cmul_to(a[j], p1);
+        else cmul_to(a[j], p0);
+    });
+    pin_tile(a);
+}
+
 // Diagonal table with one or two register bits MA, MB (0: none) at the table
 // index bits named in `aux`.
 template <typename T, int R, uint32_t MA, uint32_t MB, typename V>
@@ -182,14 +200,7 @@ __device__ __forceinline__ void diag_regs(V (&a)[1 << R], const T* __restrict__ 
         p2 = ldc(tab, (int)(ithr ^ ib));
         p3 = ldc(tab, (int)(ithr ^ ia ^ ib));
     }
-    sfor<(1 << R)>([&](auto jc) {
-        constexpr uint32_t j = decltype(jc)::value;
-        if constexpr ((j & MA) && (j & MB)) cmul_to(a[j], p3);
-        else if constexpr ((j & MB) != 0u) cmul_to(a[j], p2);
-        else if constexpr ((j & MA) != 0u) cmul_to(a[j], p1);
-        else cmul_to(a[j], p0);
-    });
-    pin_tile(a);
+    mul_slots<R, MA, MB>(a, p0, p1, p2, p3);
 }
 
 template <int B, int R, uint32_t M, uint32_t VAL, typename V>
@@ -546,19 +557,24 @@ __device__ __forceinline__ void reg_tile(typename CxT<T>::V* __restrict__ st, co
                 return ph;
             };
             auto tab_of = [&]() { return coef + op.coef; };
+            // value of a table index bit outside the registers (enc_bit)
+            auto bit_of = [&](uint32_t src) {
+                return (((uint32_t)(wave << 6 | lane) >> (src & 31u)) & (src >> 5 & 1u)) |
+                       ((uint32_t)(base >> (src >> 6 & 63u)) & (src >> 12 & 1u));
+            };
             // table index of the bits outside the registers (flipped register bits start at 1)
             auto ithr_of = [&]() {
                 uint32_t idx = (uint32_t)op.aux >> 8 & 63u;
 #pragma unroll
                 for (int q = 0; q < 6; ++q) {
                     if (q >= (op.aux & 255)) break;
-                    const int cls = op.pos[q] >> 8, v = op.pos[q] & 255;
-                    if (cls == SRC_LANE) idx |= (uint32_t)((lane >> v) & 1) << q;
-                    else if (cls == SRC_WAVE) idx |= (uint32_t)((wave >> v) & 1) << q;
-                    else if (cls == SRC_GLOB) idx |= (uint32_t)((base >> v) & 1ull) << q;
+                    idx |= bit_of((uint32_t)op.pos[q]) << q;
                 }
                 return idx;
             };
+            // bits 0 and 1 of a table held in the record (its entries: `full`)
+            auto lo_of = [&]() { return bit_of((uint32_t)op.aux & 8191u) != 0; };
+            auto hi_of = [&]() { return bit_of((uint32_t)op.aux >> 13) != 0; };
             auto full = [&](V (&m)[4]) {
                 if constexpr (sizeof(T) == 4) {
                     for (int e = 0; e < 4; ++e) m[e] = V{op.k[2 * e], op.k[2 * e + 1]};
@@ -590,7 +606,10 @@ __device__ __forceinline__ void reg_tile(typename CxT<T>::V* __restrict__ st, co
     QOPS_SHEAR_CASE(B, 1, 0) QOPS_SHEAR_CASE(B, 1, 1) QOPS_SHEAR_CASE(B, 1, 2)                               \
     QOPS_COND_CASES((B < R), RC_SIGN1 + 2 * B, RC_PHASE1 + 2 * B, 1u << B, 0u)                               \
     QOPS_COND_CASES((B < R), RC_SIGN1 + 2 * B + 1, RC_PHASE1 + 2 * B + 1, 1u << B, 1u << B)                  \
-    QOPS_CASE_IF(RC_DIAG1 + B, (B < R), (diag_regs<T, R, 1u << B, 0u>(a, tab_of(), ithr_of(), op.aux)))
+    QOPS_CASE_IF(RC_DIAG1 + B, (B < R), (diag_regs<T, R, 1u << B, 0u>(a, tab_of(), ithr_of(), op.aux)))      \
+    QOPS_CASE_IF(RC_TAB1 + B, (B < R), V m[4]; full(m); const bool lo = lo_of();                             \
+                 const V p0 = csel(lo, m[1], m[0]); const V p1 = csel(lo, m[3], m[2]);                       \
+                 (mul_slots<R, 1u << B, 0u>(a, p0, p1, p0, p1)))
 #define QOPS_COND_CASES(COND, SIGN, PHASE, M, VAL)                                                           \
     QOPS_CASE_IF(SIGN, COND, (sign_slots<R, M, VAL>(a, sign_of())))                                          \
     QOPS_CASE_IF(PHASE, COND, (phase_slots<R, M, VAL>(a, phase_of())))
@@ -598,6 +617,8 @@ __device__ __forceinline__ void reg_tile(typename CxT<T>::V* __restrict__ st, co
     QOPS_PAIR_VALUE(B, C, 0) QOPS_PAIR_VALUE(B, C, 1) QOPS_PAIR_VALUE(B, C, 2) QOPS_PAIR_VALUE(B, C, 3)      \
     QOPS_CASE_IF(RC_DIAG2 + C * (C - 1) / 2 + B, (C < R),                                                    \
                  (diag_regs<T, R, 1u << B, 1u << C>(a, tab_of(), ithr_of(), op.aux)))                        \
+    QOPS_CASE_IF(RC_TAB2 + C * (C - 1) / 2 + B, (C < R), V m[4]; full(m);                                    \
+                 (mul_slots<R, 1u << B, 1u << C>(a, m[0], m[1], m[2], m[3])))                                \
     QOPS_CX_CASE(B, C, 0) QOPS_CX_CASE(B, C, 1)
 #define QOPS_PAIR_VALUE(B, C, P)                                                                             \
     QOPS_COND_CASES((C < R), RC_SIGN2 + 4 * (C * (C - 1) / 2 + B) + P,                                       \
@@ -635,6 +656,8 @@ __device__ __forceinline__ void reg_tile(typename CxT<T>::V* __restrict__ st, co
             QOPS_LANE_1Q(0) QOPS_LANE_1Q(1) QOPS_LANE_1Q(2)
             QOPS_COND_CASES(true, RC_SIGN0, RC_PHASE0, 0u, 0u)
             QOPS_CASE_IF(RC_DIAG0, true, (phase_slots<R, 0u, 0u>(a, ldc(tab_of(), (int)ithr_of()))))
+            QOPS_CASE_IF(RC_TAB0, true, V m[4]; full(m); const bool lo = lo_of();
+                         (phase_slots<R, 0u, 0u>(a, csel(hi_of(), csel(lo, m[3], m[2]), csel(lo, m[1], m[0])))))
             case RC_SIGN: {
                 const T sgn = sign_of();
                 sfor<NR>([&](auto jc) {
@@ -659,16 +682,15 @@ __device__ __forceinline__ void reg_tile(typename CxT<T>::V* __restrict__ st, co
             case RC_DIAG: {
                 const T* tab = tab_of();
                 const uint32_t ithr = ithr_of();
-                uint32_t rm[6];
-#pragma unroll
-                for (int q = 0; q < 6; ++q) rm[q] = q < (op.aux & 255) && op.pos[q] >> 8 == SRC_REG ? 1u << (op.pos[q] & 255) : 0u;
+                uint32_t off[NR];       // index bits that differ from slot 0's
+                off[0] = 0;
+                sfor<NR>([&](auto jc) {
+                    constexpr uint32_t j = decltype(jc)::value;
+                    if constexpr (j > 0) off[j] = off[j & (j - 1)] ^ (op.ctl >> 8 * __builtin_ctz(j) & 63u);
+                });
                 sfor<NR>([&](auto jc) {
                     constexpr int j = decltype(jc)::value;
-                    uint32_t idx = ithr;
-#pragma unroll
-                    for (int q = 0; q < 6; ++q)
-                        if ((uint32_t)j & rm[q]) idx ^= 1u << q;
-                    cmul_to(a[j], ldc(tab, (int)idx));
+                    cmul_to(a[j], ldc(tab, (int)(ithr ^ off[j])));
                 });
                 pin_tile(a);
                 break;

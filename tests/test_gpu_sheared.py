@@ -141,3 +141,32 @@ def test_row_swaps(q, prec, tol, n, tile_upper, kind):
     got = sim.state().astype(np.complex128)
     sim.close()
     assert np.max(np.abs(got - orc.run_circuit(circ))) <= tol
+
+
+@pytest.mark.parametrize("prec,tol", [(0, 2e-5), (1, 1e-12)])
+@pytest.mark.parametrize("n,tile_upper", [(10, 0), (12, 0), (14, 4), (14, 5), (14, 6), (14, 7)])
+def test_diagonal_tables(q, prec, tol, n, tile_upper):
+    """Tables of 1 to 6 bits with bits in lanes, registers (exchanged or not),
+    waves and outside the tile, in ascending and descending order: the ones in
+    a record and the ones in the coefficient array.  Every entry of a table is
+    different, so a swapped bit shows."""
+    rng = np.random.default_rng(7 * n + tile_upper)
+    g = [W.Gate("u3", (b,), (), (1.0 + 0.1 * b, 0.2, 0.5)) for b in range(n)]
+    for i in range(60):
+        k = 1 + i % 6
+        w = [int(v) for v in rng.choice(n, k, replace=False)]
+        if k == 1:
+            g.append(W.Gate("p", (w[0],), (), (float(rng.uniform(0, 6.28)),)))
+        for j in range(k - 1):
+            g.append(W.Gate("rzz", (w[j], w[j + 1]), (), (float(rng.uniform(0, 6.28)),)))
+            g.append(W.Gate("rz", (w[j],), (), (float(rng.uniform(0, 6.28)),)))
+        for b in (int(v) for v in rng.choice(n, 3, replace=False)):
+            g.append(W.Gate(("u3", "rx", "ry")[i % 3], (b,), (),
+                            tuple(map(float, rng.uniform(0, 6.28, 3 if i % 3 == 0 else 1)))))
+    circ = W.Circuit(n, g, x0=9)
+    sim = q.Simulator(n, prec)
+    sim.init_basis(circ.x0)
+    sim.run(q.Plan(n, circ.gates, precision=prec, tile_upper=tile_upper))
+    got = sim.state().astype(np.complex128)
+    sim.close()
+    assert np.max(np.abs(got - orc.run_circuit(circ))) <= tol
