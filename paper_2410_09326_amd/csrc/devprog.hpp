@@ -70,8 +70,7 @@ static_assert(sizeof(DevOp) == 64, "DevOp layout");
 enum RegCode : int32_t {
     RC_NOP = 0,            // also pads the program by one record
     RC_REMAP = 1,          // registers -> LDS -> registers        aux = new mapping
-    RC_X_LANE = 2,         // exact X on lane bit aux; + 1: controls outside the registers, + 2: any controls
-    RC_1Q_LANE = 5,        // full 2x2 on lane bit aux; + 1, + 2 as above
+    RC_1Q_LANE = 5,        // full 2x2 on lane bit aux; + 1: controls outside the registers, + 2: any controls
     RC_X_REG = 8,          // + 3 register bit; + 1, + 2 as above
     RC_1Q_REG = 23,        // + 3 register bit; + 1, + 2 as above
     RC_SHEAR_REG = 38,     // + 6 register bit + 3 form + type (0 complex, 1 real, 2 imaginary)
@@ -102,7 +101,8 @@ enum RegCode : int32_t {
     RC_TAB0 = 277,         // no register bit
     RC_TAB1 = 278,         // + register bit, which is bit 1
     RC_TAB2 = 283,         // + pair number, the lower register bit is bit 0
-    RC_COUNT = 293
+    RC_X_LANE = 293,       // exact X, + 3 lane bit; + 1, + 2 as RC_1Q_LANE
+    RC_COUNT = 311
 };
 
 template <typename T>

@@ -1227,8 +1227,7 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
             else pp.n_reg_ops++;
             if (!is_x) pp.flops += 16.0 * std::ldexp(1.0, p.n);
             if (is_x) {
-                d.code = lane ? RC_X_LANE : RC_X_REG + 3 * rb;
-                d.aux = b;
+                d.code = lane ? RC_X_LANE + 3 * b : RC_X_REG + 3 * rb;
             } else if (ch.shear[pp.lop[i]]) {
                 Cl w, v;
                 int form, fl = 0;
@@ -1265,7 +1264,7 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
                 const int cb = __builtin_ctz(d.c_reg), lo = std::min(cb, rb), hi = std::max(cb, rb);
                 d.code = RC_CX_REG + 2 * (2 * pair_no(lo, hi) + (rb == hi ? 1 : 0)) + (d.c_val ? 1 : 0);
             } else if (is_x) {
-                d.code = (lane ? (int)RC_X_LANE : RC_X_REG + 3 * rb) + c;
+                d.code = (lane ? RC_X_LANE + 3 * o.t[0] : RC_X_REG + 3 * rb) + c;
             } else {
                 d.code = (lane ? (int)RC_1Q_LANE : RC_1Q_REG + 3 * rb) + c;
                 if (!lane && (flip >> rb & 1u)) d.set({o.m[3], o.m[2], o.m[1], o.m[0]});   // on exchanged slots

@@ -170,3 +170,28 @@ def test_diagonal_tables(q, prec, tol, n, tile_upper):
     got = sim.state().astype(np.complex128)
     sim.close()
     assert np.max(np.abs(got - orc.run_circuit(circ))) <= tol
+
+
+@pytest.mark.parametrize("prec,tol", [(0, 2e-5), (1, 1e-12)])
+@pytest.mark.parametrize("n,tile_upper", [(10, 0), (14, 4), (14, 5), (14, 6), (14, 7)])
+def test_x_on_lanes(q, prec, tol, n, tile_upper):
+    """X on each lane bit, alone and under controls in lanes, registers, waves
+    and outside the tile (one and two of them)."""
+    g = [W.Gate("u3", (b,), (), (1.0 + 0.1 * b, 0.2, 0.5)) for b in range(n)]
+    for b in range(6):
+        g += [W.Gate("cz", (b, (b + 1) % 6)), W.Gate("x", (b,)), W.Gate("cp", (b, n - 1), (), (0.4,))]
+        for c in range(n):
+            if c == b:
+                continue
+            g.append(W.Gate("cx", (c, b)))
+            g.append(W.Gate("cp", (b, (b + 3) % 6), (), (0.2 + 0.1 * c,)))
+            if c % 3 == 0 and (c + 5) % n != b:
+                g.append(W.Gate("x", (b,), (c, (c + 5) % n)))
+                g.append(W.Gate("ry", (b,), (), (0.3,)))
+    circ = W.Circuit(n, g, x0=6)
+    sim = q.Simulator(n, prec)
+    sim.init_basis(circ.x0)
+    sim.run(q.Plan(n, circ.gates, precision=prec, tile_upper=tile_upper))
+    got = sim.state().astype(np.complex128)
+    sim.close()
+    assert np.max(np.abs(got - orc.run_circuit(circ))) <= tol
