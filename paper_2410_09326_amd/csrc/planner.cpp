@@ -1506,21 +1506,27 @@ static size_t lds_budget(int prec);
 // bodies, more waves); a large one by its passes and vector instructions, so
 // it gets R = 4.  Measured (us per circuit; (R, W) = tile of 6 + R + W bits):
 //   complex64   (4,0)  (3,2)  (3,3)  (4,2)  (4,3)
-//   17q mix       143    125    128    148    161
-//   20q mix       236    198    188    200    206
-//   22q mix       358    437    406    333    321
-//   25q mix      2307   2768   2740   2106   2184
-//   28q QAOA    16872  14973  13481  12195  11749
-//   28q QFT+40  80903  95373  99678  69330  68978
+//   17q mix       141    122    125    139    150
+//   20q mix       229    191    181    192    196
+//   22q mix       357    417    385    310    301
+//   25q mix      2229   2607   2667   1963   2067
+//   28q QAOA    16862  14725  13141  11929  11112
+//   28q QFT+40  80437  93560  98375  69151  68454
 //   complex128
-//   18q mix       157    131    141    160    168
-//   21q mix       321    293    288    295    279
-//   25q mix      5197   4469   4054   4219   4767
+//   18q mix       152    128    139    153    161
+//   21q mix       320    294    279    276    260
+//   25q mix      5200   4435   4055   4104   4599
+// (4,3) against (4,2), complex64, mean of mix, layered, Clifford+T, QFT and
+// QAOA circuits: -7 % at 22 qubits and -4 % at 23 (two rounds of work-groups at
+// most on the chip, and fewer launches), +1 % at 24 to 27 (the state is in the
+// last-level cache or a few times its size, a wider tile only adds exchanges),
+// -2 % at 28 and 29 and -3 % at 30 (passes bound by HBM, fewer of them).
 static void reg_variant(int n, int prec, int up, int& R, int& W)
 {
     const int U = std::min(up > 0 ? up : 6, n - 6);
     if (up <= 0) {
-        // the default width: (3,2) for latency-bound states, then six bits
+        // the default width: (3,2) for latency-bound states, then six bits or
+        // (complex64) seven
         const int small = prec == QOPS_C64 ? 18 : 19;
         if (n > 12 && n <= small) {
             R = 3;
@@ -1529,7 +1535,7 @@ static void reg_variant(int n, int prec, int up, int& R, int& W)
         }
         if (U >= 6) {
             R = prec == QOPS_C64 && n >= 22 ? 4 : 3;
-            W = 6 - R;
+            W = prec == QOPS_C64 && (n == 22 || n == 23 || n >= 28) ? 3 : 6 - R;
             return;
         }
     }

@@ -195,3 +195,25 @@ def test_x_on_lanes(q, prec, tol, n, tile_upper):
     got = sim.state().astype(np.complex128)
     sim.close()
     assert np.max(np.abs(got - orc.run_circuit(circ))) <= tol
+
+
+@pytest.mark.parametrize("n,tile_upper", [(21, 7), (22, 6), (23, 6), (24, 7)])
+def test_default_width_against_another(q, n, tile_upper):
+    """The default register tile on both sides of the sizes where its width
+    changes, against an explicit other width: the same state to rounding
+    (both within 2e-5 of the oracle by the other tests, so within 4e-5 here)."""
+    rng = np.random.default_rng(n)
+    g = []
+    for _ in range(4):
+        g += [W.Gate("u3", (b,), (), tuple(map(float, rng.uniform(0, 6.28, 3)))) for b in range(n)]
+        p = [int(v) for v in rng.permutation(n)]
+        g += [W.Gate(("cz", "cx", "rzz")[i % 3], (p[2 * i], p[2 * i + 1]), (), (0.7,) if i % 3 == 2 else ())
+              for i in range(n // 2)]
+    out = []
+    for up in (0, tile_upper):
+        sim = q.Simulator(n, 0)
+        sim.init_basis(7)
+        sim.run(q.Plan(n, g, precision=0, tile_upper=up))
+        out.append(sim.state())
+        sim.close()
+    assert np.max(np.abs(out[0] - out[1])) <= 4e-5
