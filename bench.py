@@ -46,7 +46,7 @@ PASS_NAMES = {0: "tile_pass_kernel", 1: "tile_lds_kernel", 2: "state_lds_kernel"
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("kernels.hip", "planner.cpp"):
+    for f in ("kernels.hip", "regtile.hip", "planner.cpp"):
         with open(os.path.join(ROOT, "paper_2410_09326_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

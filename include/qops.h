@@ -407,9 +407,9 @@ int32_t qops_profile_create(int32_t n, qops_profile** out);
 /* Many small, uneven circuits (a parameter sweep, paper Sec. IV-E: the same
  * ansatz simulated again and again with new angles) run as ONE graph launch:
  * circuits of up to small_max_n qubits each run start to finish in one
- * work-group's LDS; the larger ones are planned into tile passes (register
- * or LDS tiles) and the graph nodes of step p run pass p of every circuit
- * that has one, one node per kernel kind.  Every circuit starts in
+ * work-group (registers or LDS); the larger ones are planned into tile passes
+ * (register or LDS tiles) and the graph nodes of step p run pass p of every
+ * circuit that has one, one node per kernel kind.  Every circuit starts in
  * |0..0>; the outputs are <Z_q> of every logical qubit of every circuit
  * (FP64, deterministic), concatenated in circuit order (sum of n_i doubles).
  * SWAP gates are handled virtually. */
@@ -420,7 +420,7 @@ typedef struct qops_batch {
     const size_t* n_gates;
     int32_t precision;             /* QOPS_C64 / QOPS_C128                      */
     void* stream;                  /* hipStream_t; null = a private stream      */
-    int32_t small_max_n;           /* whole-state-in-LDS limit (0 = 13 / 12)    */
+    int32_t small_max_n;           /* one-work-group limit (0 = 13 / 12)        */
     int32_t tile_bits;             /* tile size 2^tile_bits of the larger ones
                                       (0 = 13 / 12)                             */
     int32_t max_fuse_k;            /* block fusion width (as in qops_plan_opts;

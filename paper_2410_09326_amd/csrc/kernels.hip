@@ -1,14 +1,12 @@
 // State-vector kernels for gfx950 (CDNA4, wave64).
 //
-// Tile pass (the "chunk segment" of the paper's storage simulator, Sec. II-B,
-// mapped onto the GPU memory hierarchy): a work-group owns a tile of 2^L
-// amplitudes.  Tile positions 0..5 are physical bits 0..5 and are held one
-// per lane, so every load/store of a wave is 64 consecutive amplitudes;
-// gates on those bits use cross-lane shuffles.  The upper positions are split
-// into R register bits (gates applied in registers) and W wave bits (changed
-// by a remap through LDS).  Dense k-qubit blocks run on the LDS copy of the
-// tile, on the vector ALU or on matrix cores (MFMA, 16x16x4 f32 / f64).
-// One read and one write of the state per pass, however many gates it holds.
+// LDS tile pass (the "chunk segment" of the paper's storage simulator, Sec.
+// II-B, mapped onto the GPU memory hierarchy): a work-group owns a tile of 2^L
+// amplitudes in LDS; dense k-qubit blocks run on it, on the vector ALU or on
+// matrix cores (MFMA, 16x16x4 and 32x32x2 f32, 16x16x4 f64).  One read and one
+// write of the state per pass, however many gates it holds.  Also the
+// whole-state kernel, the gate-wise sweeps, bit exchanges and the batched
+// executor's LDS kernels.  (Passes without dense blocks: regtile.hip.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -935,7 +933,7 @@ hipError_t launch_tile_lds(int prec, void* state, const PassHdr* hdr, const DevO
     // static LDS block; the planner keeps tile plus coefficients within it)
     const int block = prec == 0 ? QOPS_LDS_TILE_BYTES_C64 : QOPS_LDS_TILE_BYTES_C128;
     if (lds_bytes > block) return hipErrorInvalidValue;
-    const int per_cu = std::max(1, tile_max_lds_bytes() / block);
+    const int per_cu = std::max(1, 160 * 1024 / block);   // work-groups by LDS
     uint64_t grid = std::min<uint64_t>(ntiles, (uint64_t)num_cus() * per_cu);
     if (grid_cap > 0 && grid > (uint64_t)grid_cap) grid = (uint64_t)grid_cap;
     if (grid == 0) grid = 1;

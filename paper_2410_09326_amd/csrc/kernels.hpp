@@ -7,20 +7,13 @@
 
 namespace qops {
 
-// Tile kernel variants (register bits R, wave bits W): tile bits L = 6+R+W.
-struct TileVariant {
-    int R, W;
-};
-bool tile_variant_supported(int prec, int R, int W);
-int tile_max_lds_bytes();
-
-// One fused tile pass.  `hdr`, `ops`, `coef` are device pointers; `lds_bytes`
+// One fused tile pass (register bits R, wave bits W): tiles of 6+R+W bits.  `hdr`, `ops`, `coef` are device pointers; `lds_bytes`
 // is the dynamic LDS the pass needs (0 when it has no LDS op).
 hipError_t launch_tile_pass(int prec, int R, int W, void* state, const PassHdr* hdr, const DevOp* ops,
                             const void* coef, uint64_t ntiles, int lds_bytes, int grid_cap, hipStream_t s);
 
-// LDS tile pass (dense blocks): tile of 2^L amplitudes in LDS, 256 threads,
-// in one static LDS block per work-group (80 KiB complex64, 160 KiB
+// LDS tile pass (dense blocks): tile of 2^L amplitudes in LDS, 256 threads
+// (512 on the largest complex128 tile), in one static LDS block per work-group (80 KiB complex64, 160 KiB
 // complex128); `lds_bytes` (tile plus staged coefficients) must fit in it,
 // else hipErrorInvalidValue.  hoist_k: qubits of the block whose fragments
 // stay in registers (hdr->hoist), 0 if none.

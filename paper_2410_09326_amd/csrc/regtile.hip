@@ -823,17 +823,6 @@ template hipError_t launch_batch_reg_t<QOPS_RT_T, QOPS_RT_R, QOPS_RT_W>(const Ba
 
 namespace qops {
 
-bool tile_variant_supported(int prec, int R, int W)
-{
-#define QOPS_CHECK(r, w) if (R == r && W == w) return true;
-    (void)prec;
-    QOPS_TILE_VARIANTS(QOPS_CHECK)
-#undef QOPS_CHECK
-    return false;
-}
-
-int tile_max_lds_bytes() { return 160 * 1024; }
-
 hipError_t launch_tile_pass(int prec, int R, int W, void* state, const PassHdr* hdr, const DevOp* ops,
                             const void* coef, uint64_t ntiles, int lds_bytes, int grid_cap, hipStream_t s)
 {
