@@ -948,6 +948,7 @@ struct Chain {
     Cl d0[64], d1[64];
     bool waits[64] = {false};
     long double scale = 1.0;    // factor the current pass still owes
+    bool last = false;          // no register tile pass follows
     Chain()
     {
         for (int b = 0; b < 64; ++b) d0[b] = d1[b] = Cl(1);
@@ -986,6 +987,54 @@ static int coef_type(const Cl& w, const Cl& v)
     if (w.im == 0 && v.im == 0) return 1;
     if (w.re == 0 && v.re == 0) return 2;
     return 0;
+}
+
+// A coefficient as the kernel holds it.
+static double stored(double x, int prec) { return prec == QOPS_C64 ? (double)(float)x : x; }
+static Cl stored(const Cl& a, int prec) { return {stored((double)a.re, prec), stored((double)a.im, prec)}; }
+
+// What rounding the entries does to the norm of an amplitude that meets each
+// alike; it joins the store's factor.
+template <typename E>
+static long double rounding_factor(const E* e, size_t n, int prec)
+{
+    long double was = 0, is = 0;
+    for (size_t i = 0; i < n; ++i) {
+        was += norm2(Cl(e[i]));
+        is += norm2(stored(Cl(e[i]), prec));
+    }
+    return was < 2 * is && is < 2 * was ? std::sqrt(was / is) : 1.0L;
+}
+
+// The factor d for which d (s0, s1) is nearest to the row (n0, n1).
+static Cl fit_row(const Cl& n0, const Cl& n1, const Cl& s0, const Cl& s1)
+{
+    const Cl c0(s0.re, -s0.im), c1(s1.re, -s1.im), a = n0 * c0, b = n1 * c1;
+    const long double n = norm2(s0) + norm2(s1);
+    return {(a.re + b.re) / n, (a.im + b.im) / n};
+}
+
+// The kernel applies w and v rounded to the state's precision, which would
+// scale the two output rows by the rounding errors: the same for every
+// amplitude, and for every qubit under one angle, so it would add up in the
+// norm.  The waiting diagonal is fitted to the rounded rows instead.
+static void round_reg_form(const Cl (&N)[4], int form, int flip, int prec, Cl& w, Cl& v, Cl& d0, Cl& d1)
+{
+    w = stored(w, prec);
+    v = stored(v, prec);
+    const Cl vw = v * w, one(1), f(1 + vw.re, vw.im);
+    // rows of slots 0 and 1: the first step's slot is x + w y, the other's y + v (x + w y)
+    const Cl r0[2] = {form == 0 ? one : f, form == 0 ? w : v};
+    const Cl r1[2] = {form == 0 ? v : w, form == 0 ? f : one};
+    d0 = flip ? fit_row(N[0], N[1], r1[0], r1[1]) : fit_row(N[0], N[1], r0[0], r0[1]);
+    d1 = flip ? fit_row(N[2], N[3], r0[0], r0[1]) : fit_row(N[2], N[3], r1[0], r1[1]);
+}
+static void round_lane_form(const Cl (&N)[4], int ex, int prec, Cl& w, Cl& v, Cl& d0, Cl& d1)
+{
+    w = stored(w, prec);
+    v = stored(v, prec);
+    d0 = ex ? fit_row(N[0], N[1], w, Cl(1)) : fit_row(N[0], N[1], Cl(1), w);
+    d1 = ex ? fit_row(N[2], N[3], Cl(1), v) : fit_row(N[2], N[3], v, Cl(1));
 }
 
 // Form of a sheared 2x2 on a register bit: N maps the slots (0, 1) to bit
@@ -1236,13 +1285,16 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
                     // the kernel pairs the lanes' rows through register bit 0,
                     // whose slots an exchanged form leaves exchanged
                     shear_reg_form(N, form, fl, w, v, ch.d0[b], ch.d1[b]);
+                    round_reg_form(N, form, fl, p.prec, w, v, ch.d0[b], ch.d1[b]);
                     flip ^= (uint32_t)fl;
                     d.code = RC_SHEAR_ROW + 12 * (b - 4) + 6 * fl + 3 * form + coef_type(w, v);
                 } else if (lane) {
                     shear_lane_form(N, form, w, v, ch.d0[b], ch.d1[b]);
+                    round_lane_form(N, form, p.prec, w, v, ch.d0[b], ch.d1[b]);
                     d.code = RC_SHEAR_LANE + 6 * b + 3 * form + coef_type(w, v);
                 } else {
                     shear_reg_form(N, form, fl, w, v, ch.d0[b], ch.d1[b]);
+                    round_reg_form(N, form, fl, p.prec, w, v, ch.d0[b], ch.d1[b]);
                     flip |= (uint32_t)fl << rb;
                     d.code = RC_SHEAR_REG + 6 * rb + 3 * form + coef_type(w, v);
                 }
@@ -1251,6 +1303,7 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
                 d.code = lane ? RC_1Q_LANE : RC_1Q_REG + 3 * rb;
                 d.aux = b;
                 d.set({N[0].to_cd(), N[1].to_cd(), N[2].to_cd(), N[3].to_cd()});
+                ch.scale *= rounding_factor(N, 4, p.prec);
             }
         } else if (o.kind == LOp::ONEQ) {
             const bool lane = o.t[0] < 6, is_x = exact_x(o.m);
@@ -1291,6 +1344,8 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
                 d.code = sign ? RC_SIGN : RC_PHASE;
             }
             d.set({ph});
+            // (it meets 2^-k of the amplitudes)
+            ch.scale *= 1 + (rounding_factor(&ph, 1, p.prec) - 1) / (1 << o.k);
             pp.n_diag_ops++;
             pp.flops += 6.0 * std::ldexp(1.0, p.n - o.k);
         } else {   // DIAG
@@ -1344,6 +1399,7 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
                 }
                 d.coef = push_coef(p, o.m);
             }
+            ch.scale *= rounding_factor(&o.m[0], o.m.size(), p.prec);
             pp.n_diag_ops++;
             pp.flops += 6.0 * std::ldexp(1.0, p.n);
         }
@@ -1362,8 +1418,12 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
         ch.scale *= g;
     }
     h.flip = (int32_t)flip;
-    h.scale = (double)ch.scale;
-    ch.scale = 1.0;
+    // A factor of a few units in the last place of 1 does not multiply evenly
+    // (1 - 2^-24 takes a whole unit off every amplitude), so it waits until it
+    // has grown or the last pass; what rounding it leaves goes on as well.
+    const bool waits = !ch.last && std::abs(ch.scale - 1) < (p.prec == QOPS_C64 ? 0x1p-20L : 0x1p-49L);
+    h.scale = waits ? 1.0 : stored((double)ch.scale, p.prec);
+    ch.scale /= h.scale;
     h.lds_bytes = W > 0 ? (1 << pp.L) * (p.prec == 0 ? 8 : 16) : 0;
     pp.op0 = h.op0;
     pp.op_stride = stride;
@@ -1629,7 +1689,11 @@ static void emit_passes(Plan& p)
         if (pp.type == PASS_TILE_REG && pp.W > 0) order_for_registers(p, pp);
     Chain ch;
     find_chains(p, ch);
+    const PassPlan* last = nullptr;
+    for (const PassPlan& pp : p.passes)
+        if (pp.type == PASS_TILE_REG) last = &pp;
     for (PassPlan& pp : p.passes) {
+        ch.last = &pp == last;
         if (pp.type == PASS_TILE_LDS) emit_tile_lds(p, pp);
         else if (pp.type == PASS_TILE_REG) emit_tile_reg(p, pp, ch);
     }

@@ -217,3 +217,22 @@ def test_default_width_against_another(q, n, tile_upper):
         out.append(sim.state())
         sim.close()
     assert np.max(np.abs(out[0] - out[1])) <= 4e-5
+
+
+@pytest.mark.parametrize("n", [12, 16, 20])
+@pytest.mark.parametrize("angle", [0.3, 0.9, 1.7, 2.6])
+def test_one_angle_on_every_qubit_keeps_the_norm(q, n, angle):
+    """The rounding of a 2x2's coefficients is the same for every qubit under
+    one angle, so it must not add up in the norm: what is left is one rounded
+    factor a pass and a few units of the last place (2^-24 each)."""
+    g = [W.Gate("h", (b,)) for b in range(n)]
+    for layer in range(4):
+        g += [W.Gate("rzz", (b, (b + 1) % n), (), (0.37 + 0.1 * b + layer,)) for b in range(n)]
+        g += [W.Gate("rx" if layer % 2 else "ry", (b,), (), (angle,)) for b in range(n)]
+    sim = q.Simulator(n, 0)
+    sim.init_basis(0)
+    p = q.Plan(n, g, precision=0)
+    sim.run(p)
+    norm = np.linalg.norm(sim.state().astype(np.complex128))
+    sim.close()
+    assert abs(norm - 1) <= (p.stats()["n_passes"] + 6) * 2.0 ** -24
