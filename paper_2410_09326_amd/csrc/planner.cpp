@@ -1275,9 +1275,14 @@ static void emit_tile_reg(Plan& p, PassPlan& pp, Chain& ch)
             if (lane) pp.n_lane_ops++;
             else pp.n_reg_ops++;
             if (!is_x) pp.flops += 16.0 * std::ldexp(1.0, p.n);
+            // the lane form takes up to half of |d0 d1| per operation, which the
+            // amplitudes hold instead: the full 2x2 gives it back before they
+            // leave the range of the state's type (an operation in 65 at most,
+            // 2^-33 a bit and 2^66 in the amplitudes at worst)
+            const bool grown = norm2(N[0] * N[3] - N[1] * N[2]) < 0x1p-64L;
             if (is_x) {
                 d.code = lane ? RC_X_LANE + 3 * b : RC_X_REG + 3 * rb;
-            } else if (ch.shear[pp.lop[i]]) {
+            } else if (ch.shear[pp.lop[i]] && !grown) {
                 Cl w, v;
                 int form, fl = 0;
                 ch.waits[b] = true;

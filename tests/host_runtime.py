@@ -1,0 +1,88 @@
+"""The library on a fake HIP runtime (tests/fake_hip.cpp), one check per run:
+python host_runtime.py FAKE_LIBRARY CHECK.  The fake's symbols have to come
+before the real runtime's, so a check needs a process of its own."""
+import ctypes
+import os
+import struct
+import sys
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+
+CALLBACK = ctypes.CFUNCTYPE(None, ctypes.c_int, ctypes.c_char_p, ctypes.c_uint64, ctypes.c_uint64,
+                            ctypes.POINTER(ctypes.c_void_p))
+RC_1Q_LANE, RC_1Q_REG, RC_SHEAR_REG = 5, 23, 38    # operation codes (devprog.hpp)
+
+
+def argument(args, i, ctype):
+    return ctypes.cast(args[i], ctypes.POINTER(ctype))[0]
+
+
+def tile_pass(args, prec):
+    """A register tile pass: the factor of its store and its operations as
+    (code, entries)."""
+    hdr = ctypes.string_at(argument(args, 1, ctypes.c_void_p), 240)
+    ops = argument(args, 2, ctypes.c_void_p)
+    nops, op0 = struct.unpack("2i", hdr[12:20])
+    size = 64 if prec == 0 else 128
+    recs = []
+    for i in range(nops):
+        r = ctypes.string_at(ops + 64 * op0 + size * i, size)
+        k = struct.unpack("8f", r[24:56]) if prec == 0 else struct.unpack("8d", r[24:56] + r[64:96])
+        recs.append((struct.unpack("i", r[:4])[0], [complex(k[2 * e], k[2 * e + 1]) for e in range(4)]))
+    return struct.unpack("d", hdr[232:240])[0], recs
+
+
+class Fake:
+    def __init__(self, path):
+        self.lib = ctypes.CDLL(path, ctypes.RTLD_GLOBAL)
+        self.on_launch = lambda index, kernel, grid, block, args: None
+        self._cb = CALLBACK(lambda i, k, g, b, a: self.on_launch(i, k.decode(), g, b, a))
+        self.lib.fake_on_launch(self._cb)
+
+
+def state(q, n, prec, stream=None):
+    h = ctypes.c_void_p()
+    q.check(q.lib().qops_create(n, prec, None, 0, stream, ctypes.byref(h)))
+    return h
+
+
+def deep_layers(n, busy, layers, gate):
+    g = []
+    for _ in range(layers):
+        g += [(gate[0], (b,), gate[1]) for b in range(busy)]
+        g += [("cz", (b, b + 1)) for b in range(busy - 1)]
+    return g
+
+
+def check_growth(fake, q):
+    """A chain of 2x2s keeps the amplitudes in range: what its operations have
+    not applied yet (the next full 2x2 or the pass's store does) stays above
+    2^-17 on each bit, 2^-66 in all."""
+    seen = []
+
+    def on_launch(i, kernel, grid, block, args):
+        if "tile_pass_kernel" in kernel:
+            seen.append(tile_pass(args, prec))
+    fake.on_launch = on_launch
+    for prec in (0, 1):
+        for n, busy, up in ((10, 10, 0), (11, 11, 0), (12, 12, 0), (13, 4, 7), (20, 4, 0)):
+            for gate in (("h", ()), ("rx", (1.5707963267948966,)), ("u3", (1.2, 0.3, 2.2))):
+                seen.clear()
+                p = q.Plan(n, deep_layers(n, busy, 400, gate), precision=prec, tile_upper=up)
+                h = state(q, n, prec)
+                q.check(q.lib().qops_run_plan(h, p.handle))
+                assert seen
+                for scale, recs in seen:
+                    assert scale >= 2.0 ** -66, (prec, n, gate, scale)
+                    for code, k in recs:
+                        if RC_1Q_LANE <= code < RC_1Q_LANE + 3 or RC_1Q_REG <= code < RC_SHEAR_REG:
+                            assert max(abs(x) for x in k) >= 2.0 ** -17, (prec, n, gate, code, k)
+                q.lib().qops_destroy(h)
+
+
+if __name__ == "__main__":
+    f = Fake(sys.argv[1])
+    import paper_2410_09326_amd._binding as qops
+    globals()["check_" + sys.argv[2]](f, qops)
+    print("ok", sys.argv[2], flush=True)
