@@ -35,7 +35,7 @@ struct qops_batch_exec {
         int kind = 0;                   // 0: register tiles (R, W), 1: LDS tiles
         int R = 0, W = 0;
         int lds = 0;                    // dynamic LDS bytes
-        bool whole = false;             // whole-state tiles: a branch of its own
+        bool whole = false;             // whole-state tiles: on their split's branch
         std::vector<BatchItem> items;
         BatchItem* d = nullptr;
     };
@@ -68,8 +68,7 @@ struct qops_batch_exec {
 
 namespace {
 
-// Runs start to finish in the LDS kernel (the others run in tile passes, of
-// which a state in one register tile has one).
+// Runs start to finish in the LDS kernel (the others run in tile passes).
 bool lds_circuit(const qops_batch_exec* e, const Plan& p)
 {
     return p.n <= e->small_max_n && (p.passes.empty() || p.passes[0].type == PASS_STATE_LDS);
@@ -279,9 +278,12 @@ hipError_t enqueue_node(qops_batch_exec* e, const qops_batch_exec::Node& nd, hip
 }
 
 // The LDS circuits and the whole-state tiles are long programs on few
-// work-groups, so each of their kernels is a branch beside the tile passes of
-// the larger circuits (96 circuits of 10..20 qubits: 3.59 ms in one line,
-// 2.96 ms in branches); all join before the <Z> reduction.
+// work-groups, so they are branches beside the tile passes of the larger
+// circuits (96 circuits of 10..20 qubits: 3.59 ms in one line, 2.96 ms in
+// branches): one for the LDS circuits and one per register/wave split of the
+// whole-state tiles, which runs that split's nodes in the order of their
+// passes (all passes of a circuit have its split).  All join before the <Z>
+// reduction.
 hipError_t enqueue(qops_batch_exec* e, hipStream_t s)
 {
     size_t used = 0;
@@ -309,11 +311,18 @@ hipError_t enqueue(qops_batch_exec* e, hipStream_t s)
             er = launch_batch_small(e->prec, e->d_small, (int)e->small_ids.size(), e->d_circs, e->d_ops, e->d_coef,
                                     e->d_out, e->lds_small, b);
     }
-    for (size_t k = 0; k < e->nodes.size() && er == hipSuccess; ++k)
-        if (e->nodes[k].whole) {
+    std::vector<std::pair<const qops_batch_exec::Node*, hipStream_t>> splits;
+    for (size_t k = 0; k < e->nodes.size() && er == hipSuccess; ++k) {
+        const qops_batch_exec::Node& nd = e->nodes[k];
+        if (!nd.whole) continue;
+        auto sp = std::find_if(splits.begin(), splits.end(),
+                               [&](const auto& x) { return x.first->R == nd.R && x.first->W == nd.W; });
+        if (sp == splits.end()) {
             er = branch(b);
-            if (er == hipSuccess) er = enqueue_node(e, e->nodes[k], b);
+            sp = splits.insert(splits.end(), {&nd, b});
         }
+        if (er == hipSuccess) er = enqueue_node(e, nd, sp->second);
+    }
     for (size_t k = 0; k < e->nodes.size() && er == hipSuccess; ++k)
         if (!e->nodes[k].whole) er = enqueue_node(e, e->nodes[k], s);
     // every branch joins, also after an error (a capture must not leave one open)

@@ -33,6 +33,15 @@ def tile_pass(args, prec):
     return struct.unpack("d", hdr[232:240])[0], recs
 
 
+def sweep(n, depth, seed=0.1):
+    g = []
+    for d in range(depth):
+        for b in range(n):
+            g += [("ry", (b,), (seed + 0.01 * b + d,)), ("rz", (b,), (seed - 0.02 * b + d,))]
+        g += [("cz", (b, b + 1)) for b in range(d & 1, n - 1, 2)]
+    return g
+
+
 class Fake:
     def __init__(self, path):
         self.lib = ctypes.CDLL(path, ctypes.RTLD_GLOBAL)
@@ -79,6 +88,44 @@ def check_growth(fake, q):
                         if RC_1Q_LANE <= code < RC_1Q_LANE + 3 or RC_1Q_REG <= code < RC_SHEAR_REG:
                             assert max(abs(x) for x in k) >= 2.0 ** -17, (prec, n, gate, code, k)
                 q.lib().qops_destroy(h)
+
+
+def check_batch_order(fake, q):
+    """In a batch's stream order and in its graph a circuit's pass p ends
+    before its pass p + 1 begins, and every pass before the <Z> reduction."""
+    runs = []
+
+    def on_launch(i, kernel, grid, block, args):
+        if not runs or (runs[-1] and runs[-1][-1][2] == "z"):
+            runs.append([])                      # the eager run, then the capture
+        if "tile_pass_kernel" in kernel:
+            items = argument(args, 5, ctypes.c_void_p)
+            count = argument(args, 4, ctypes.c_uint64)
+            circs = {struct.unpack("2i", ctypes.string_at(items + 8 * j, 8))[0] for j in range(count)}
+            runs[-1].append((i, circs, argument(args, 7, ctypes.c_int32)))
+        elif "batch_zfinal" in kernel:
+            runs[-1].append((i, None, "z"))
+    fake.on_launch = on_launch
+    dense = [("dense", (0, 1), (), (), [[1, 0, 0, 0], [0, 0, 1, 0], [0, 1, 0, 0], [0, 0, 0, 1]])]
+    for prec in (0, 1):
+        for circs in ([(13, sweep(13, d)) for d in (24, 64, 128)], [(12, sweep(12, 160)), (13, sweep(13, 40))],
+                      [(n, sweep(n, d)) for n, d in ((8, 5), (10, 300), (11, 200), (12, 3), (12, 130), (13, 70), (15, 9))] +
+                      [(11, sweep(11, 2) + dense)]):
+            runs.clear()
+            b = q.Batch(circs, precision=prec)
+            assert len(runs) == 2
+            for run in runs:
+                last = {}
+                for i, cs, step in run:
+                    if step == "z":
+                        assert all(fake.lib.fake_ordered(j, i) for j, c, s in run if s != "z")
+                        continue
+                    for c in cs:
+                        assert step == (last[c][1] + 1 if c in last else 0), (prec, c, step)
+                        assert c not in last or fake.lib.fake_ordered(last[c][0], i), (prec, c, step)
+                        last[c] = (i, step)
+                assert last
+            b.close()
 
 
 if __name__ == "__main__":
