@@ -1829,8 +1829,9 @@ static void pack(Plan& p)
         bool lds_full;
         if (p.prec == 0) {
             // complex64: the widest 5/6-qubit matrix-core block stays in
-            // registers; everything else must fit the LDS budget next to the
-            // tile (two work-groups per CU)
+            // registers; everything else of an LDS pass must fit the LDS
+            // budget next to the tile (two work-groups per CU).  A register
+            // tile pass stages nothing
             const bool big = o.kind == LOp::DENSE && o.k >= 5 && use_mfma_for(p, o.k, Lt);
             bool ok = true;
             if (big) {
@@ -1846,7 +1847,7 @@ static void pack(Plan& p)
                     ok = false;               // a second 6-qubit block does not fit
                 }
             }
-            lds_full = !ok || nstaged + tile_bytes > lds_budget(0);
+            lds_full = d2 && (!ok || nstaged + tile_bytes > lds_budget(0));
         } else {
             // complex128 passes keep all their fragments in LDS (one
             // work-group per CU)

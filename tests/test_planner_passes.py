@@ -1,0 +1,15 @@
+"""How the planner cuts circuits into passes (no GPU needed)."""
+import pytest
+
+import paper_2410_09326_amd as q
+from workloads import circuits as W
+
+
+# A register tile pass stages no coefficients in LDS, so the LDS beside the
+# tile must not end it.
+@pytest.mark.parametrize("n,depth,up", [(13, 21, 7), (13, 128, 7), (12, 140, 0), (10, 300, 0)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_whole_state_tile_is_one_pass(n, depth, up, prec):
+    c = W.param_sweep_batch(seed=depth, count=1, nmin=n, nmax=n, dmin=depth, dmax=depth)[0]
+    p = q.Plan(n, c.gates, precision=prec, tile_upper=up)
+    assert [x["type"] for x in p.passes()] == [0]
