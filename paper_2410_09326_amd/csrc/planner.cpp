@@ -1643,16 +1643,23 @@ static void finish_pass(Plan& p, PassPlan& pp, uint64_t upmask, bool dense)
 // An operation may run once every earlier one it does not commute with has
 // (neither's non-diagonal target meets the other's bits).  The register set
 // follows emit_tile_reg's choice: the next R distinct upper targets in the new
-// order, then the bits held so far.
+// order, then the bits held so far.  It looks among the first 512 operations
+// that wait: a pass of a large state has 257 at most, and one that holds a
+// small state's whole circuit is ordered in time linear in its length.
 static void order_for_registers(Plan& p, PassPlan& pp)
 {
-    const int nl = (int)pp.lop.size();
+    const int nl = (int)pp.lop.size(), window = 512;
     std::vector<uint64_t> touch(nl), nd(nl);
+    uint64_t all_nd = 0, all_diag = 0;     // targets, and bits of the diagonal operations
     for (int i = 0; i < nl; ++i) {
         touch[i] = p.lops[pp.lop[i]].touch();
         nd[i] = p.lops[pp.lop[i]].tmask();
+        all_nd |= nd[i];
+        if (nd[i] == 0) all_diag |= touch[i];
     }
-    std::vector<char> done(nl, 0);
+    std::vector<int> next(nl + 1);         // list of the waiting operations; next[nl]: the first
+    for (int i = 0; i < nl; ++i) next[i] = i + 1;
+    next[nl] = 0;
     std::vector<int> out;
     out.reserve(nl);
     const uint64_t upper = ~63ull;
@@ -1664,19 +1671,23 @@ static void order_for_registers(Plan& p, PassPlan& pp)
         while (moved) {
             moved = false;
             uint64_t bt = 0, bn = 0;       // bits of the operations still waiting
-            for (int i = 0; i < nl; ++i) {
-                if (done[i]) continue;
+            int waiting = 0;
+            for (int prev = nl, i = next[nl]; i < nl && waiting < window; i = next[prev]) {
                 const bool ready = (nd[i] & bt) == 0 && (touch[i] & bn) == 0;
                 const uint64_t need = nd[i] & upper;
                 const bool fits = (need & ~regs) == 0 || __builtin_popcountll(regs | need) <= pp.R;
                 if (ready && fits) {
                     regs |= need;
-                    done[i] = 1;
                     out.push_back(pp.lop[i]);
+                    next[prev] = next[i];
                     moved = true;
                 } else {
                     bt |= touch[i];
                     bn |= nd[i];
+                    ++waiting;
+                    prev = i;
+                    // every target and every diagonal has to wait
+                    if ((all_nd & ~bt) == 0 && (all_diag & ~bn) == 0) break;
                 }
             }
         }
@@ -1803,8 +1814,11 @@ static void pack(Plan& p)
     // any bit of the other (shared bits are then controls or diagonal bits of
     // both).  A physical swap ends the scan.
     const size_t nl = p.lops.size();
-    // (a tile that holds every bit takes every operation)
-    const size_t window = cap_reg >= n - 6 ? nl : 256;
+    // (a register tile that holds every bit takes every operation)
+    const bool blocks = p.par.force_lds || std::any_of(p.lops.begin(), p.lops.end(), [](const LOp& o) {
+                            return o.kind != LOp::ONEQ && o.kind != LOp::DIAG;
+                        });
+    const size_t window = cap_reg >= n - 6 && !blocks ? nl : 256;
     std::vector<char> placed(nl, 0);
     // non-diagonal target bits outside the fixed bits of a register tile (6)
     // or of an LDS tile (4)
