@@ -144,6 +144,22 @@ void program_images(const qops_batch_exec* e, std::vector<PassHdr>& hdrs, std::v
     }
 }
 
+// Whether plan b fits the offsets, nodes and LDS sizes laid out for plan a.
+bool same_layout(const Plan& a, const Plan& b)
+{
+    if (a.dops.size() != b.dops.size() || a.coef.size() != b.coef.size() || a.hdrs.size() != b.hdrs.size() ||
+        a.passes.size() != b.passes.size())
+        return false;
+    for (size_t i = 0; i < a.passes.size(); ++i) {
+        const PassPlan &x = a.passes[i], &y = b.passes[i];
+        if (x.type != y.type || x.R != y.R || x.W != y.W || x.L != y.L) return false;
+        // fixed at creation: an LDS circuit's operations, an LDS pass's coefficients
+        if (x.type == PASS_STATE_LDS && (x.op0 != y.op0 || x.nops != y.nops)) return false;
+        if (x.type == PASS_TILE_LDS && a.hdrs[x.hdr].coef_n != b.hdrs[y.hdr].coef_n) return false;
+    }
+    return true;
+}
+
 int32_t layout(qops_batch_exec* e)
 {
     const size_t asz = e->prec == QOPS_C64 ? 8 : 16, csz = asz / 2;
@@ -468,20 +484,23 @@ int32_t qops_batch_update(qops_batch_exec* e, const qops_gate* const* gates, con
 {
     try {
         if (!e || !gates || !n_gates) return set_error(QOPS_INVALID_ARG, "null argument");
+        // all or nothing: the plans are replaced once every circuit fits
+        std::vector<Plan> fresh(e->count);
+        for (int i = 0; i < e->count; ++i) {
+            Err er = rebuild_plan(e->plans[i], gates[i], n_gates[i], fresh[i]);
+            if (!er.ok()) return set_error(er.code, "circuit " + std::to_string(i) + ": " + er.msg);
+            if (!same_layout(e->plans[i], fresh[i]))
+                return set_error(QOPS_BAD_STATE, "circuit " + std::to_string(i) + ": new parameters change the plan");
+        }
+        e->plans.swap(fresh);
         const size_t csz = e->prec == QOPS_C64 ? 4 : 8;
         std::vector<unsigned char> cimg;
         size_t total = 0;
         for (int i = 0; i < e->count; ++i) total = std::max(total, e->coef_base[i] + e->plans[i].coef.size());
         cimg.assign(std::max<size_t>(total, 1) * csz, 0);
         for (int i = 0; i < e->count; ++i) {
-            qops::Plan& p = e->plans[i];
-            const size_t before_ops = p.dops.size(), before_coef = p.coef.size(), before_hdrs = p.hdrs.size();
-            Err er = update_plan(p, gates[i], n_gates[i]);
-            if (!er.ok()) return set_error(er.code, "circuit " + std::to_string(i) + ": " + er.msg);
-            if (p.dops.size() != before_ops || p.coef.size() != before_coef || p.hdrs.size() != before_hdrs)
-                return set_error(QOPS_BAD_STATE, "circuit " + std::to_string(i) + ": new parameters change the plan");
-            if (e->prec == QOPS_C64) cast_coef<float>(p.coef, cimg, e->coef_base[i]);
-            else cast_coef<double>(p.coef, cimg, e->coef_base[i]);
+            if (e->prec == QOPS_C64) cast_coef<float>(e->plans[i].coef, cimg, e->coef_base[i]);
+            else cast_coef<double>(e->plans[i].coef, cimg, e->coef_base[i]);
         }
         // the sheared operations' forms and the pass factors follow the values
         std::vector<PassHdr> hdrs;

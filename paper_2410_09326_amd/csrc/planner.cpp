@@ -2100,7 +2100,7 @@ Err lower_gates(int n, const qops_gate* g, size_t ng, int swap_mode, std::vector
     return lower(n, g, ng, swap_mode, l2p, out, nvirt);
 }
 
-Err update_plan(Plan& p, const qops_gate* g, size_t ng)
+Err rebuild_plan(const Plan& p, const qops_gate* g, size_t ng, Plan& q)
 {
     if (ng != p.gates.size()) return mkerr(QOPS_BAD_STATE, "gate count differs from the plan");
     for (size_t i = 0; i < ng; ++i) {
@@ -2116,14 +2116,21 @@ Err update_plan(Plan& p, const qops_gate* g, size_t ng)
     }
     // Re-plan with identical structure: merging decisions depend only on the
     // structure, except identity cancellation, which is re-evaluated.
-    Plan q;
     Err e = build_plan(p.n, p.prec, p.l2p_in.data(), g, ng, p.par, q);
+    if (!e.ok()) return e;
+    q.predicted_s = p.predicted_s;
+    return Err{};
+}
+
+Err update_plan(Plan& p, const qops_gate* g, size_t ng)
+{
+    Plan q;
+    Err e = rebuild_plan(p, g, ng, q);
     if (!e.ok()) return e;
     std::swap(q.d_hdr, p.d_hdr);
     std::swap(q.d_ops, p.d_ops);
     std::swap(q.d_coef, p.d_coef);
     std::swap(q.d_bytes, p.d_bytes);
-    q.predicted_s = p.predicted_s;
     p = std::move(q);
     p.dirty = true;
     return Err{};

@@ -167,6 +167,8 @@ Err lower_gates(int n, const qops_gate* g, size_t ng, int swap_mode, std::vector
 // Plans already-lowered operations on an n-bit state in identity layout
 // (merging, fusion, packing, device program); `ops` is consumed.
 Err plan_from_lops(int n, int prec, std::vector<LOp>& ops, const PlanParams& par, Plan& p);
+// The plan of the same circuit with new angles/matrices (same structure).
+Err rebuild_plan(const Plan& p, const qops_gate* g, size_t ng, Plan& q);
 // Rebinds angles/matrices (same structure) and re-emits coefficients.
 Err update_plan(Plan& p, const qops_gate* g, size_t ng);
 
