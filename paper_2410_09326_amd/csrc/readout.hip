@@ -95,8 +95,9 @@ probs_kernel(const typename Row<T>::V* __restrict__ st, ProbsArgs a, double* __r
     constexpr int RB = Row<T>::kRowBits, PER = RB - 8 + 1;   // amplitudes per access
     __shared__ double tab[1 << RB];
     const int t = threadIdx.x;
-    const uint64_t slice = blockIdx.x & ((1u << a.slice_bits) - 1u);
-    const uint64_t high = (uint64_t)(blockIdx.x >> a.slice_bits);
+    const uint32_t block = blockIdx.y * gridDim.x + blockIdx.x;
+    const uint64_t slice = block & ((1u << a.slice_bits) - 1u);
+    const uint64_t high = block >> a.slice_bits;
     const uint64_t base = deposit64(slice, a.slice_mask) | deposit64(high, a.marg_mask);
     const bool in = a.n >= RB || (t * PER) < (1 << a.n);     // smaller states fill part of a row
     double s0 = 0.0, s1 = 0.0;
@@ -441,13 +442,16 @@ hipError_t launch_probs(int prec, const void* state, int n, int m, const int* po
     }
     ProbsArgs a;
     probs_geometry(prec, n, m, pos, a);
-    const unsigned grid = 1u << (a.n_high + a.slice_bits);
+    // one dimension of a dispatch holds fewer than 2^32 work-items, which 24
+    // marginal high bits exceed: the numbers above 2^20 go to the second one
+    const int bits = a.n_high + a.slice_bits, xbits = std::min(bits, 20);
+    const dim3 grid(1u << xbits, 1u << (bits - xbits));
     double* dst = a.slice_bits > 0 ? scratch : out;
     if (prec == 0)
-        hipLaunchKernelGGL(probs_kernel<float>, dim3(grid), dim3(kThreads), 0, st,
+        hipLaunchKernelGGL(probs_kernel<float>, grid, dim3(kThreads), 0, st,
                            reinterpret_cast<const Amp2*>(state), a, dst);
     else
-        hipLaunchKernelGGL(probs_kernel<double>, dim3(grid), dim3(kThreads), 0, st,
+        hipLaunchKernelGGL(probs_kernel<double>, grid, dim3(kThreads), 0, st,
                            reinterpret_cast<const double2*>(state), a, dst);
     if (a.slice_bits > 0) {
         const uint32_t ny = 1u << m;

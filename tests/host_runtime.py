@@ -156,6 +156,26 @@ def check_batch_update(fake, q):
     assert fake.lib.fake_bad_copies() == 0
 
 
+def check_marginal_launches(fake, q):
+    """Marginals over many bits of the largest states launch (a dispatch takes
+    fewer than 2^32 work-items), also when every marginal bit is a high one."""
+    import numpy as np
+    launched = []
+    fake.on_launch = lambda i, kernel, grid, block, args: launched.append((kernel, grid))
+    for n, prec, m in ((32, 1, 24), (33, 0, 24), (33, 1, 24), (33, 1, 25), (34, 0, 25), (34, 1, 25), (34, 0, 12),
+                       (30, 0, 21), (20, 0, 8)):
+        h = ctypes.c_void_p()
+        # a borrowed state that no kernel here reads
+        q.check(q.lib().qops_create(n, prec, 4096, 16 << n, None, ctypes.byref(h)))
+        out = np.zeros(1 << m)
+        for qubits in (range(n - m, n), range(m)):
+            launched.clear()
+            q.check(q.lib().qops_probabilities(h, (ctypes.c_int32 * m)(*qubits), m,
+                                               out.ctypes.data_as(ctypes.POINTER(ctypes.c_double))))
+            assert any("probs_kernel" in k for k, g in launched), (n, prec, m)
+        q.lib().qops_destroy(h)
+
+
 if __name__ == "__main__":
     f = Fake(sys.argv[1])
     import paper_2410_09326_amd._binding as qops
