@@ -420,7 +420,8 @@ typedef struct qops_batch {
     const size_t* n_gates;
     int32_t precision;             /* QOPS_C64 / QOPS_C128                      */
     void* stream;                  /* hipStream_t; null = a private stream      */
-    int32_t small_max_n;           /* one-work-group limit (0 = 13 / 12)        */
+    int32_t small_max_n;           /* one-work-group limit (0 = 13 / 12, else
+                                      9 at least)                               */
     int32_t tile_bits;             /* tile size 2^tile_bits of the larger ones
                                       (0 = 13 / 12)                             */
     int32_t max_fuse_k;            /* block fusion width (as in qops_plan_opts;

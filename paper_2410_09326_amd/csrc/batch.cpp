@@ -384,7 +384,8 @@ int32_t qops_batch_create(const qops_batch* b, qops_batch_exec** out)
         e->prec = b->precision;
         e->count = b->count;
         const int lds_cap = b->precision == QOPS_C64 ? 13 : 12;
-        e->small_max_n = b->small_max_n > 0 ? std::min(b->small_max_n, lds_cap) : lds_cap;
+        // (a register tile has 10 bits at least, so no smaller state runs in one)
+        e->small_max_n = b->small_max_n > 0 ? std::max(9, std::min(b->small_max_n, lds_cap)) : lds_cap;
         e->tile_bits = b->tile_bits > 0 ? std::min(b->tile_bits, lds_cap) : lds_cap;
         if (e->tile_bits > e->small_max_n + 1) e->tile_bits = e->small_max_n + 1;
         if (e->tile_bits < 10) e->tile_bits = 10;

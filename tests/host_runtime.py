@@ -3,6 +3,7 @@ python host_runtime.py FAKE_LIBRARY CHECK.  The fake's symbols have to come
 before the real runtime's, so a check needs a process of its own."""
 import ctypes
 import os
+import re
 import struct
 import sys
 
@@ -174,6 +175,42 @@ def check_marginal_launches(fake, q):
                                                out.ctypes.data_as(ctypes.POINTER(ctypes.c_double))))
             assert any("probs_kernel" in k for k, g in launched), (n, prec, m)
         q.lib().qops_destroy(h)
+
+
+def check_tile_shapes(fake, q):
+    """Every register tile pass is launched with the kernel of its tile: 6 + R
+    + W bits, no more than the state has."""
+    def on_launch(i, kernel, grid, block, args):
+        m = re.search(r"tile_pass_kernelI[fd]Li(\d)ELi(\d)E", kernel)
+        if not m:
+            return
+        bits = 6 + int(m.group(1)) + int(m.group(2))
+        hdr = argument(args, 1, ctypes.c_void_p)
+        items = argument(args, 5, ctypes.c_void_p)
+        at = set()
+        if items:
+            circs = argument(args, 6, ctypes.c_void_p)
+            for j in range(argument(args, 4, ctypes.c_uint64)):
+                c = struct.unpack("2i", ctypes.string_at(items + 8 * j, 8))[0]
+                at.add(struct.unpack("i", ctypes.string_at(circs + 40 * c + 16, 4))[0] + argument(args, 7, ctypes.c_int32))
+        for k in at or {0}:
+            n, tile = struct.unpack("2i", ctypes.string_at(hdr + 240 * k, 8))
+            shapes.append((n, tile, bits))
+    fake.on_launch = on_launch
+    shapes = []
+    for prec in (0, 1):
+        for small in (5, 8, 9, 10, 0):
+            for bits in (0, 10, 12):
+                q.Batch([(n, sweep(n, 2)) for n in range(1, 16)], precision=prec, small_max_n=small, tile_bits=bits).close()
+        for n in (*range(1, 15), 18, 20, 22, 23):
+            for up in range(0, 9):
+                p = q.Plan(n, sweep(n, 2), precision=prec, tile_upper=up)
+                h = state(q, n, prec)
+                q.check(q.lib().qops_run_plan(h, p.handle))
+                q.lib().qops_destroy(h)
+    assert shapes
+    wrong = {x for x in shapes if not (x[2] == x[1] <= x[0])}
+    assert not wrong, wrong
 
 
 if __name__ == "__main__":
