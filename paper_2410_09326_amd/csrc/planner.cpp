@@ -1106,6 +1106,42 @@ static bool exact_x(const Mat& m)
 
 static int pair_no(int lo, int hi) { return hi * (hi - 1) / 2 + lo; }
 
+// Register bits a tile needs for each operation code (a variant compiles only
+// the bodies of its own register bits); 99: no body.
+struct RegCodeBits {
+    uint8_t need[RC_COUNT];
+    RegCodeBits()
+    {
+        std::memset(need, 99, sizeof(need));
+        auto plain = [&](int first, int count) { std::memset(need + first, 0, count); };
+        auto by_bit = [&](int first, int per) {
+            for (int b = 0; b < 5; ++b) std::memset(need + first + per * b, b + 1, per);
+        };
+        auto by_pair = [&](int first, int per) {
+            for (int hi = 1; hi < 5; ++hi)
+                for (int lo = 0; lo < hi; ++lo) std::memset(need + first + per * pair_no(lo, hi), hi + 1, per);
+        };
+        plain(RC_REMAP, 1);
+        plain(RC_1Q_LANE, 3);
+        plain(RC_SHEAR_LANE, 24);
+        plain(RC_SHEAR_ROW, 24);
+        plain(RC_X_LANE, 18);
+        for (int c : {RC_DIAG, RC_DIAG0, RC_PHASE, RC_PHASE0, RC_SIGN, RC_SIGN0, RC_TAB0}) plain(c, 1);
+        by_bit(RC_X_REG, 3);
+        by_bit(RC_1Q_REG, 3);
+        by_bit(RC_SHEAR_REG, 6);
+        by_bit(RC_DIAG1, 1);
+        by_bit(RC_TAB1, 1);
+        by_bit(RC_PHASE1, 2);
+        by_bit(RC_SIGN1, 2);
+        by_pair(RC_DIAG2, 1);
+        by_pair(RC_TAB2, 1);
+        by_pair(RC_PHASE2, 4);
+        by_pair(RC_SIGN2, 4);
+        by_pair(RC_CX_REG, 4);
+    }
+};
+
 // One operation record of a register tile pass, in either precision.
 struct RegRec {
     int code = RC_NOP;
@@ -1936,6 +1972,18 @@ static Err finish_plan(Plan& p, std::vector<LOp>& lowered, std::chrono::steady_c
         fuse_blocks(p.lops, std::min(par.max_fuse_k, 6));
     }
     pack(p);
+    // register tile kernels: a tile of the variant's size, operations that it
+    // has bodies for, and LDS where they exchange through it
+    static const RegCodeBits bits;
+    for (const PassPlan& pp : p.passes) {
+        if (pp.type != PASS_TILE_REG) continue;
+        bool ok = pp.L == 6 + pp.R + pp.W && pp.L <= p.n && (int)pp.up.size() == pp.R + pp.W;
+        for (int k = 0; k < pp.nops; ++k) {
+            const int code = p.dops[pp.op0 + (size_t)k * pp.op_stride].type;   // RegOpT::code
+            ok = ok && code >= 0 && code < RC_COUNT && bits.need[code] <= pp.R && (code != RC_REMAP || pp.W > 0);
+        }
+        if (!ok) return mkerr(QOPS_UNSUPPORTED, "internal: a register tile pass does not match its kernel");
+    }
     // LDS tile kernels start each of their 256 threads on a distinct tile
     // element (tiles of at least 2^8; 512 threads only on the largest
     // complex128 tile) and read every coefficient but the hoisted block's from
