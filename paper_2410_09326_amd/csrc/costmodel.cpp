@@ -164,7 +164,9 @@ int32_t build_priced_plan(int n, int prec, const int32_t* l2p, const qops_gate* 
     const int k_lo = opts->max_fuse_k > 0 ? opts->max_fuse_k : 1;
     const int k_hi = opts->max_fuse_k > 0 ? opts->max_fuse_k : 4;
     std::vector<int> widths;
-    if (prec == QOPS_C64) widths.push_back(0);   // for complex128 the default equals width 6
+    // (from 20 qubits on complex128's default equals width 6; below, it has
+    // width 5's register tiles and width 6's LDS tiles)
+    if (prec == QOPS_C64 || n < 20) widths.push_back(0);
     for (int up = 4; up <= max_up; ++up) widths.push_back(up);
     for (int kf = k_lo; kf <= k_hi; ++kf)
         for (int remap = 0; remap <= 1; ++remap)

@@ -1,4 +1,6 @@
 """How the planner cuts circuits into passes (no GPU needed)."""
+import os
+
 import pytest
 
 import paper_2410_09326_amd as q
@@ -24,3 +26,20 @@ def test_planning_is_linear_in_a_pass(n, up, prec):
         c = W.layered_u3_cx(1, n=n, depth=layers, swap_frac=0.0)
         return min(q.Plan(n, c.gates, precision=prec, tile_upper=up).stats()["plan_seconds"] for _ in range(3))
     assert seconds(6000) <= 9 * seconds(1500)
+
+
+# Priced planning never returns a plan that it prices above the default one.
+@pytest.mark.parametrize("mode", ["profiled", "learned"])
+@pytest.mark.parametrize("n", [13, 16, 18, 19, 20])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_priced_plan_against_the_default(prec, n, mode):
+    models = os.path.join(os.path.dirname(q.__file__), "models")
+    if mode == "profiled":
+        kw = {"mode": q.PLAN_PROFILED, "profile": q.Profile.load(os.path.join(models, "corpus_profile.bin"))}
+    else:
+        kw = {"mode": q.PLAN_LEARNED, "model": q.CostModel.load(os.path.join(models, "cost_mlp.bin"))}
+    for seed in range(3):
+        for c in (W.haar_blocks(seed, n, 40), W.random_mixed(seed, n, 80, max_dense_k=5), W.random_mix_layers(seed, n, 10)):
+            best = q.Plan(n, c.gates, precision=prec, **kw).stats()["predicted_s"]
+            default = q.Plan(n, c.gates, precision=prec).predict(**kw)
+            assert best <= default * (1 + 1e-12), (seed, c.name)
