@@ -286,8 +286,10 @@ int32_t qops_run_plan(qops_sim* h, const qops_plan* p);
 int32_t qops_plan_update(qops_plan* p, const qops_gate* gates, size_t n_gates);
 
 /* Paper Sec. II-B + III-D: plans (opts may be null = defaults) and runs a
- * gate list on the handle in one call; the plan is kept by the handle until
- * the next apply or destroy.  Errors as qops_plan_build.  Asynchronous. */
+ * gate list on the handle in one call; the handle keeps the device block of
+ * its program for the next call.  Errors as qops_plan_build; QOPS_HIP_ERROR
+ * while the handle's stream is being captured (run a plan there that has run
+ * before).  Asynchronous. */
 int32_t qops_apply(qops_sim* h, const qops_gate* gates, size_t n_gates, const qops_plan_opts* opts);
 
 /* --------------------------------------------------------- profiling ---- */

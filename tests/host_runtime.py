@@ -46,6 +46,8 @@ def sweep(n, depth, seed=0.1):
 class Fake:
     def __init__(self, path):
         self.lib = ctypes.CDLL(path, ctypes.RTLD_GLOBAL)
+        self.lib.fake_stream.restype = ctypes.c_void_p
+        self.lib.fake_capture.argtypes = [ctypes.c_void_p, ctypes.c_int]
         self.on_launch = lambda index, kernel, grid, block, args: None
         self._cb = CALLBACK(lambda i, k, g, b, a: self.on_launch(i, k.decode(), g, b, a))
         self.lib.fake_on_launch(self._cb)
@@ -211,6 +213,32 @@ def check_tile_shapes(fake, q):
     assert shapes
     wrong = {x for x in shapes if not (x[2] == x[1] <= x[0])}
     assert not wrong, wrong
+
+
+def check_capture(fake, q):
+    """While the handle's stream is captured, in every mode, a gate list is
+    refused without a call that breaks the capture, and a plan that has run
+    before launches its passes."""
+    s = ctypes.c_void_p(fake.lib.fake_stream())
+    count = []
+    fake.on_launch = lambda *a: count.append(a[1])
+    h = state(q, 14, 0, s)
+    gates = sweep(14, 3)
+    ga = q.GateArray(gates)
+    p = q.Plan(14, gates, precision=0)
+    q.check(q.lib().qops_run_plan(h, p.handle))
+    passes = len(count)
+    for mode in (0, 1, 2):
+        fake.lib.fake_capture(s, mode)
+        blocks = fake.lib.fake_blocks()
+        assert q.lib().qops_apply(h, ga.ptr(), ga.n, None) == -6          # QOPS_HIP_ERROR
+        assert fake.lib.fake_blocks() == blocks and fake.lib.hipGetLastError() == 0
+        count.clear()
+        q.check(q.lib().qops_run_plan(h, p.handle))
+        assert len(count) == passes
+        fake.lib.fake_capture(s, -1)
+    q.check(q.lib().qops_apply(h, ga.ptr(), ga.n, None))
+    q.lib().qops_destroy(h)
 
 
 if __name__ == "__main__":

@@ -21,7 +21,7 @@ def fake(tmp_path_factory):
     return so
 
 
-@pytest.mark.parametrize("check", ["growth", "batch_order", "batch_update", "marginal_launches", "tile_shapes"])
+@pytest.mark.parametrize("check", ["growth", "batch_order", "batch_update", "marginal_launches", "tile_shapes", "capture"])
 def test_host(fake, check):
     r = subprocess.run([sys.executable, os.path.join(HERE, "host_runtime.py"), fake, check], capture_output=True,
                        text=True, timeout=300)
