@@ -1,7 +1,7 @@
 // Batched executor: many small, uneven circuits (parameter sweeps, paper
 // Sec. IV-E) in one graph launch.  Circuits whose whole state fits one
-// work-group run start to finish in one kernel (as one register tile, or in
-// LDS where they have fewer than 10 qubits or dense blocks);
+// work-group run start to finish in one kernel (as one register tile, in one
+// pass, or in LDS where they have fewer than 10 qubits or dense blocks);
 // the larger ones are planned into tile passes (register tiles, or LDS tiles
 // where a pass holds dense blocks) and pass p of every circuit that has one
 // runs in the graph nodes of step p, one node per kernel kind.  <Z_i> of

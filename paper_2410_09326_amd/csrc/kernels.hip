@@ -1181,10 +1181,6 @@ __device__ __forceinline__ double block_sum_256(double v, double* sh)
     return r;
 }
 
-struct PosArr {
-    int p[QOPS_MAX_QUBITS_DEV];
-};
-
 // ---------------------------------------------------------------------------
 // Logical-order gather (readout through the layout map)
 // ---------------------------------------------------------------------------

@@ -51,6 +51,11 @@ size_t zsum_bounded_scratch_doubles(int n);
 hipError_t launch_expect_z_bounded(int prec, const void* state, int n, const int32_t* l2p, double* scratch,
                                    double* out, hipStream_t s);
 
+// Physical positions of logical bits, as a kernel argument.
+struct PosArr {
+    int p[QOPS_MAX_QUBITS_DEV];
+};
+
 // Marginal over physical bits pos[0..m-1] (host array); out: 2^m doubles
 // (device).  scratch must hold probs_scratch_doubles(prec, n, m, pos) doubles.
 size_t probs_scratch_doubles(int prec, int n, int m, const int* pos);

@@ -917,13 +917,16 @@ static void emit_lds_op(Plan& p, const LOp& o, int L, F tpos, PassPlan& pp, bool
 
 // Sheared 2x2 operations of the register tile kernel.  A 2x2 M on a bit that
 // an uncontrolled 2x2 targets again (no other non-diagonal operation on the
-// bit in between) is replaced by a product of two triangular steps that cost
-// half of M's multiply-adds; M = (exchange) diag(d0, d1) (steps).  The
-// diagonal commutes with every operation up to that next 2x2 (controls,
-// phases, other bits), which absorbs it into its own matrix, and the last 2x2
-// of each such chain is applied in full.  `pend` holds the diagonal waiting on
-// each physical bit, with |d0 d1| = 1 at pass ends (the common factor moves to
-// the pass's store).  Everything is composed in FP64.
+// bit in between) is replaced by two steps (register bits, lane bits 4 and 5)
+// or one combination with the partner (lane bits 0..3) that cost half of M's
+// multiply-adds; M = (exchange) diag(d0, d1) (that form).  The diagonal
+// commutes with every operation up to that next 2x2 (controls, phases, other
+// bits), which absorbs it into its own matrix, and the last 2x2 of each such
+// chain is applied in full.  Chain holds the diagonal waiting on each physical
+// bit, with |d0 d1| = 1 at pass ends (the common factor moves to the pass's
+// store).  Within a pass the two-step form keeps |d0 d1|; the lane form lowers
+// it, and the amplitudes grow by as much, so a chain of lane forms is broken
+// by a full 2x2 before either leaves the type's range (emit_tile_reg).
 // The composition runs in extended precision and rounds each coefficient once,
 // so that a chain's coefficients are as exact as single matrices'.
 struct Cl {
@@ -1040,7 +1043,7 @@ static void round_lane_form(const Cl (&N)[4], int ex, int prec, Cl& w, Cl& v, Cl
 // Form of a sheared 2x2 on a register bit: N maps the slots (0, 1) to bit
 // values (0, 1).  The pivot is the larger entry of the row, so |w|, |v| stay
 // near or below 1; of the two orders the one that keeps |d1/d0| nearer to 1
-// is taken, so the waiting diagonals stay within a factor of 2.
+// is taken, so that ratio stays between 1/2 and 2.
 static void shear_reg_form(const Cl (&N)[4], int& form, int& flip, Cl& w, Cl& v, Cl& d0, Cl& d1)
 {
     const Cl det = N[0] * N[3] - N[1] * N[2];
@@ -1088,7 +1091,8 @@ static void shear_reg_form(const Cl (&N)[4], int& form, int& flip, Cl& w, Cl& v,
 }
 
 // Scaled form on a lane bit (no slots to exchange: the exchanged form takes
-// the partner's amplitude as its own).
+// the partner's amplitude as its own).  |d1/d0| is as before or inverted,
+// |d0 d1| comes down by up to a half.
 static void shear_lane_form(const Cl (&N)[4], int& ex, Cl& w, Cl& v, Cl& d0, Cl& d1)
 {
     const long double c0 = norm2(N[0]) + norm2(N[2]), c1 = norm2(N[1]) + norm2(N[3]);

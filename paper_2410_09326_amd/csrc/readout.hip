@@ -178,10 +178,6 @@ probs_slices_kernel(const double* __restrict__ part, int slice_bits, uint32_t ny
     if ((threadIdx.x & 63) == 0) out[y] = v;
 }
 
-struct PosArr {
-    int p[QOPS_MAX_QUBITS_DEV];
-};
-
 // All bits marginal: a permutation of |psi|^2, no sum.
 template <typename T, typename V>
 __global__ void __launch_bounds__(kThreads) probs_direct_kernel(const V* __restrict__ st, int n, PosArr pa,

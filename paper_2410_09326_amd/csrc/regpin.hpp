@@ -1,6 +1,6 @@
 // Keeps a register tile's amplitudes in one block of vector registers.
 //
-// The tile kernel's operation loop is a switch over ~100 unrolled bodies that
+// The tile kernel's operation loop is a switch over some 300 unrolled bodies that
 // all read and write the whole tile.  Left to itself the register allocator
 // places the amplitudes one by one, differently in different bodies, and
 // joins the bodies with 100 and more register moves per operation.  An empty

@@ -93,11 +93,10 @@ __device__ __forceinline__ void cmul_to(V& a, const V b)
     cmul_tail(a.x, a.y, b.x, b.y, t, u);
 }
 
-// 2x2 on register bit B.  Register-slot controls (slots whose bits `creg`
-// equal `cval`) are compile-time per slot and uniform; `tok` is the per-lane
-// control result.
 // Exact X on register bit B: exchange the two halves (no arithmetic).
-// CTRL: 0 = none, 1 = controls outside the registers (`tok`), 2 = any.
+// CTRL: 0 = none, 1 = controls outside the registers (`tok`, the per-lane
+// result), 2 = any (and the slots whose bits `creg` equal `cval`, which is
+// uniform per slot).
 template <int B, int R, int CTRL, typename V>
 __device__ __forceinline__ void xgate_reg_b(V (&a)[1 << R], uint32_t creg, uint32_t cval, bool tok)
 {
@@ -120,6 +119,7 @@ __device__ __forceinline__ void xgate_reg_b(V (&a)[1 << R], uint32_t creg, uint3
     pin_tile(a);
 }
 
+// Full 2x2 on register bit B; CTRL as above.
 template <int B, int R, int CTRL, typename V>
 __device__ __forceinline__ void oneq_reg_b(V (&a)[1 << R], V m00, V m01, V m10, V m11, uint32_t creg, uint32_t cval, bool tok)
 {
@@ -220,8 +220,8 @@ __device__ __forceinline__ void cx_slots(V (&a)[1 << R])
 // q += v p, with p the slots whose bit is FORM (0 or 1) and q the others.
 // The 2x2 it stands for is diag(d0, d1) times this, possibly with the two
 // slots exchanged; the planner carries the diagonal into the next operation
-// on that bit and the exchange into the slot's index (DevOp::c_tile,
-// PassHdr::flip).  Both steps update in place: 4 fused multiply-adds per
+// on that bit and the exchange into later operations' slot conditions and
+// indices (RegOpT::ctl and aux) and the store (PassHdr::flip).  Both steps update in place: 4 fused multiply-adds per
 // amplitude (2 where w and v are real or imaginary) and no copies, against 8
 // and two copies for the full product.  The kernel's bound is the vector
 // ALU's issue rate, so that is its time: a 28-qubit QFT + 40 layers of U3 and

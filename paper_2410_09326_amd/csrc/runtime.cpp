@@ -101,10 +101,12 @@ void free_plan_device(Plan& p)
 }
 
 // Lends the handle's image to a plan that runs once: the copy is ordered on
-// the handle's stream behind the previous plan's passes, so nothing is
-// allocated or waited for after the first call (Clifford+T, 15 qubits, 400
-// gates in one call: 125 us a call against 290 with three allocations,
-// frees and blocking copies).
+// the handle's stream behind the previous plan's passes.  The pinned memory it
+// reads is one block, so a call waits until the previous call's copy is done,
+// that is until the passes of the call before that one have ended; a program
+// larger than any before drains the stream and allocates.  (Clifford+T, 15
+// qubits, 400 gates in one call: 123 us a call against 290 with three
+// allocations, frees and blocking copies.)
 static int32_t lend_image(qops_sim* h, Plan& p)
 {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -337,7 +339,6 @@ int32_t qops_destroy(qops_sim* h)
     if (h->image) (void)hipFree(h->image);
     if (h->stage) (void)hipHostFree(h->stage);
     if (h->stage_done) (void)hipEventDestroy(h->stage_done);
-    delete h->last_plan;
     delete h;
     return QOPS_OK;
 }
@@ -514,15 +515,12 @@ int32_t qops_apply(qops_sim* h, const qops_gate* gates, size_t n_gates, const qo
 {
     QOPS_GUARD({
         if (!h) return set_error(QOPS_INVALID_ARG, "null handle");
-        std::unique_ptr<Plan> p(new Plan());
-        int32_t rc = build_priced_plan(h->n, h->prec, h->l2p.data(), gates, n_gates, opts, *p);
+        Plan p;
+        int32_t rc = build_priced_plan(h->n, h->prec, h->l2p.data(), gates, n_gates, opts, p);
         if (rc) return rc;
-        rc = lend_image(h, *p);
+        rc = lend_image(h, p);
         if (rc) return rc;
-        rc = run_plan(h, *p);
-        delete h->last_plan;
-        h->last_plan = p.release();
-        return rc;
+        return run_plan(h, p);
     });
 }
 

@@ -19,7 +19,6 @@ struct qops_sim {
     std::vector<int> l2p;             // logical qubit -> physical bit
     double* scratch = nullptr;        // reductions / readout staging
     size_t scratch_doubles = 0;
-    qops::Plan* last_plan = nullptr;  // kept alive until the next apply / destroy
     // qops_apply's program: one device block that every call rewrites in
     // stream order, filled from pinned memory (free again once `stage_done`)
     void* image = nullptr;
