@@ -1786,8 +1786,11 @@ static void pack(Plan& p)
         return;
     }
     // a state of 10..12 qubits without dense blocks is one register tile (one
-    // work-group): 12 qubits, 360 operations in complex128 take 199 us
-    // against 611 with every operation reading and writing LDS
+    // work-group): 12 qubits, 360 operations in complex128 take 172 us against
+    // 612 with every operation reading and writing LDS.  Tiles asked for too
+    // narrow for the state are several passes, which still beat the LDS kernel
+    // (11 and 12 qubits, 4 or 5 upper bits, four circuits in both precisions:
+    // 8.7-212 against 17.5-612 us, 1.7 to 5 times)
     bool reg_state = n >= 10 && n <= p.par.state_reg;
     for (const LOp& o : p.lops) reg_state = reg_state && (o.kind == LOp::ONEQ || o.kind == LOp::DIAG);
     if (n <= p.par.state_lds_max_n && !reg_state) {

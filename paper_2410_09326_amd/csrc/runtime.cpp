@@ -105,7 +105,7 @@ void free_plan_device(Plan& p)
 // reads is one block, so a call waits until the previous call's copy is done,
 // that is until the passes of the call before that one have ended; a program
 // larger than any before drains the stream and allocates.  (Clifford+T, 15
-// qubits, 400 gates in one call: 123 us a call against 290 with three
+// qubits, 400 gates in one call: 105 us a call against 292 with three
 // allocations, frees and blocking copies.)
 static int32_t lend_image(qops_sim* h, Plan& p)
 {

@@ -1,5 +1,6 @@
-"""Batched circuits deep enough for several passes of their whole-state tile
-beside each other: <Z> against the oracle, replays, and new parameters."""
+"""Batched circuits that one work-group runs start to finish, up to 128 layers
+deep and beside each other: <Z> against the oracle, replays, new parameters;
+and every such circuit of the 512-circuit parameter sweep."""
 import numpy as np
 import pytest
 
@@ -35,3 +36,20 @@ def test_deep_batch(shape, prec, ulp):
                                  for x in c.gates]) for c in circs]
         b.update([c.gates for c in circs])
     b.close()
+
+
+def test_sweep_whole_state_circuits():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_09326_amd as q
+    circs = W.param_sweep_batch()
+    b = q.Batch([(c.n, c.gates) for c in circs], precision=q.C64)
+    b.launch()
+    res = b.results()
+    b.close()
+    whole = [i for i, c in enumerate(circs) if c.n <= 13]
+    assert len(whole) > 100
+    for i in whole:
+        c = circs[i]
+        assert np.max(np.abs(res[i] - orc.expect_z(orc.run_circuit(c)))) <= 8 * len(c.gates) * 2.0 ** -24, (i, c.n)
